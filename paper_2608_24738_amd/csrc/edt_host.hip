@@ -745,9 +745,9 @@ int run(Request &r) {
             ws.sq = s.sq;
             ws.cost = r.ws;
             ws.rows = r.shape[0];
-            // packed field: the next pass takes it, and every wave's rows pair
-            // up inside one block of that axis's rows
-            if (nd >= 2 && wsh.lpw >= 2 && r.shape[nd - 2] % wsh.lpw == 0 && !fh[nd - 2].l1long &&
+            // packed field: the next pass takes it, and every wave's rows (an
+            // even number) pair up inside one block of that axis's rows
+            if (nd >= 2 && wsh.lpw % 2 == 0 && r.shape[nd - 2] % wsh.lpw == 0 && !fh[nd - 2].l1long &&
                 !fh[nd - 2].tiled16) {
                 const FhPlan &p1 = fh[nd - 2];
                 if (mode == kScanFieldInt && p1.lp16) pkw = 16;
