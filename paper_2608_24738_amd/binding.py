@@ -205,6 +205,9 @@ def tm_edt_noalloc(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None,
 # Workspaces of the scipy-style wrapper, one per (device, stream): calls on one
 # stream run in order, so they can share it.
 _workspaces = {}
+# Columns of these lengths take the bracketed search, whose groups gain nothing
+# from a dispatch order: 8 x 1024^2 discs 66 us per call without, 72 us with one.
+_UNORDERED_ROWS = range(640, 2049)
 
 
 def _workspace(dev, nbytes: int, stream=None):
@@ -422,7 +425,9 @@ def distance_transform_edt(input: torch.Tensor, sampling=None, return_distances:
     if return_indices:
         idx_out, idx_back = _out_buffer(indices, lead + (ndim,) + spatial, torch.int32, dev, "indices")
     batch = int(lead[0]) * int(lead[1])
-    ws = _workspace(dev, tm_edt_workspace_size(ndim, spatial, batch, samp, return_indices))
+    ws = None
+    if spatial[0] not in _UNORDERED_ROWS:
+        ws = _workspace(dev, tm_edt_workspace_size(ndim, spatial, batch, samp, return_indices))
     tm_edt_ws(mask, ndim, samp, dist_out, idx_out, ws)
     if dist_back is not None:
         dist_back.copy_(dist_out)
@@ -478,7 +483,9 @@ def distance_transform_cdt(input: torch.Tensor, metric: str = "chessboard", dist
     mask = _as_mask(input)
     out, back = _out_buffer(distances, mask.shape, torch.int32, mask.device, "distances")
     batch = int(mask.shape[0]) * int(mask.shape[1])
-    ws = _workspace(mask.device, tm_cdt_workspace_size(ndim, tuple(mask.shape[2:]), batch, METRICS[metric]))
+    ws = None
+    if mask.shape[2] not in _UNORDERED_ROWS:
+        ws = _workspace(mask.device, tm_cdt_workspace_size(ndim, tuple(mask.shape[2:]), batch, METRICS[metric]))
     tm_cdt_ws(mask, ndim, METRICS[metric], out, ws)
     if back is not None:
         back.copy_(out)

@@ -41,6 +41,7 @@
 #include "edt_long.h"
 #include "edt_plane.h"
 #include "edt_lpair.h"
+#include "edt_bracket.h"
 #include "edt_order.h"
 
 using namespace tmedt;
@@ -206,6 +207,16 @@ constexpr uint64_t kPairMinLines = 256 * kPairLines;
 // whole-line search with 8 lines per workgroup.
 constexpr uint64_t kLpMinGroups = 512;
 
+// Rows from which a distance pass takes the bracketed search instead of the
+// whole-line windowed one, whose work grows with the distances.  Measured
+// (column pass, us, windowed -> bracketed): 8 x 1024^2 discs 105 -> 54, balls
+// 137 -> 67, 1 % background 30 -> 30; chessboard 90 -> 49, 124 -> 51, 22 -> 27;
+// 8 x 600 x 803 discs 63 -> 45, balls 48 -> 53, 1 % background 25 -> 23;
+// 16 x 375 x 500 discs 32 -> 36, balls 28 -> 40: shorter lines stay.  Index
+// passes take it where the tiled search ends (256 rows): the envelope with one
+// lane per line takes 516 us on 16 x 375 x 500 balls, the brackets 41 us.
+constexpr uint32_t kBkMinRows = 640;
+
 // Plan of one strided pass.
 struct FhPlan {
     uint32_t lpw;
@@ -222,6 +233,9 @@ struct FhPlan {
     bool l1long;     // taxicab, two running minima in place (k_cdt_l1_long)
     bool l1scan;     // taxicab, whole lines in LDS, prefix and suffix minima (k_cdt_l1_scan)
     bool lp16;       // 16 lines per workgroup, two per packed 16-bit word (k_line_pair16)
+    int bk;          // bracketed search (k_line_bracket): rows per segment, 0 = not
+    bool bk_key;     //   index carrier: value and row in one key
+    uint32_t fcap;   //   value of rows without sites in a key
 };
 
 // Whole-line windowed search: 8 lines per workgroup (a wave covers 8 rows
@@ -238,6 +252,32 @@ bool plan_line_search(FhPlan &p, uint32_t n, uint64_t total, bool w16, int min_l
     p.ls_lpw = lpw;
     p.ls_w16 = w16;
     p.lds = line_search_lds(n, lpw, tb);
+    return true;
+}
+
+// First strided pass by bracketed search (k_line_bracket): the field is the
+// row scan's distance, or (index) the carrier of a 2-D request.
+bool plan_bracket(FhPlan &p, const Request &r, int a, uint64_t total, bool index_path) {
+    const uint32_t n = r.shape[a], w = r.shape[r.ndim - 1];
+    if (!index_path && n < kBkMinRows) return false;
+    if (a != r.ndim - 2 || !r.unit || r.sgn || w > kBkMaxD || n > kBkMaxN || total / n + kBkLines >= (uint64_t(1) << 32))
+        return false;
+    if (index_path) {
+        if (r.ndim != 2) return false;
+        // key: value less s^2 plus S^2, at most f + (distance along the line)^2 + S^2
+        // over the rows walked (up to a guard band past the line), above the row
+        uint32_t kb = uint32_t(bits_for(n - 1));
+        if (kb < 1) kb = 1;
+        const uint64_t reach = uint64_t(n + kBkG + kBkSeg) * (n + kBkG + kBkSeg) + kBkSeg * kBkSeg + 1;
+        const uint64_t lim = (uint64_t(1) << (32 - kb)) - 1;
+        p.bk_key = uint64_t(w - 1) * (w - 1) + 2 * reach < lim;
+        p.fcap = p.bk_key ? uint32_t(lim - reach) : 0u;
+        p.rbits = kb;
+    }
+    const size_t lds = bk_lds(n, kBkSeg);
+    if (lds + 8192 > kLdsBytes) return false;
+    p.bk = kBkSeg;
+    p.lds = lds;
     return true;
 }
 
@@ -414,6 +454,7 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
                 }
                 continue;
             }
+            if (r.metric == kLinf && plan_bracket(p, r, a, total, false)) continue;
             const uint64_t cmax = r.metric == kL1 ? vmax + n + 4 : std::max<uint64_t>(vmax, n + 4);
             // taxicab lines whose 8-line groups share rows: prefix and suffix
             // minima, no search
@@ -495,6 +536,7 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
                 continue;
             }
         }
+        if (!index_path && plan_bracket(p, r, a, total, false)) continue;
         // Otherwise, unit sampling without indices: whole lines in LDS with
         // the windowed search (32-bit tile) while they fit.
         if (!index_path && r.unit && plan_line_search(p, n, total, false)) continue;
@@ -514,6 +556,7 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
                 continue;
             }
         }
+        if (index_path && !r.big && plan_bracket(p, r, a, total, true)) continue;
         const uint64_t lines = total / n;
         if (p.lpw == 0 || (lines + p.lpw - 1) / p.lpw >= (uint64_t(1) << 31)) {
             // the field carrier has no kernel for this line; the index
@@ -569,7 +612,7 @@ OrderPlan order_groups(const Request &r, const FhPlan *fh, uint64_t total) {
     if (r.ndim != 2 || !r.unit || r.big || r.idx || r.sgn) return {0, 0};
     // k_line_search orders units of four groups of 8 lines (32 columns)
     const uint32_t width = (fh[0].lp16 && r.metric == kL2) ? uint32_t(kLpLines)
-                           : (!fh[0].tiled16 && !fh[0].l1long && fh[0].ls_lpw == 8) ? 32u : 0u;
+                           : (!fh[0].tiled16 && !fh[0].l1long && (fh[0].ls_lpw == 8 || fh[0].bk)) ? 32u : 0u;
     if (!width) return {0, 0};
     const uint32_t n0 = r.shape[0], nlast = r.shape[1];
     if (nlast % kWave != 0 || nlast > uint32_t(kWave * kWave) || nlast / width > 256) return {0, 0};
@@ -713,7 +756,7 @@ int run(Request &r) {
             s.cstride = cstride;
             out = cidx;
         } else if (r.unit) {
-            mode = kScanFieldInt;
+            mode = fh[nd - 2].bk ? kScanFieldL1 : kScanFieldInt;
             s.field_i = r.dist ? reinterpret_cast<int32_t *>(r.dist) : r.sq;
             out = s.field_i;
         } else {
@@ -745,12 +788,12 @@ int run(Request &r) {
             ws.sq = s.sq;
             ws.cost = r.ws;
             ws.rows = r.shape[0];
-            // packed field: the next pass takes it, and every wave's rows (an
-            // even number) pair up inside one block of that axis's rows
+            // packed field: the next pass takes it, and every wave's rows pair
+            // up (an even number of them) inside one block of that axis's rows
             if (nd >= 2 && wsh.lpw % 2 == 0 && r.shape[nd - 2] % wsh.lpw == 0 && !fh[nd - 2].l1long &&
                 !fh[nd - 2].tiled16) {
                 const FhPlan &p1 = fh[nd - 2];
-                if (mode == kScanFieldInt && p1.lp16) pkw = 16;
+                if ((mode == kScanFieldInt && p1.lp16) || (mode == kScanFieldL1 && p1.bk)) pkw = 16;
                 else if ((mode == kScanFieldInt || mode == kScanFieldL1) && !p1.lp16 && (p1.ls_lpw == 8 || p1.l1scan))
                     pkw = 8;
             }
@@ -776,8 +819,10 @@ int run(Request &r) {
                     else rc = TM_WORD(kScanFieldInt);
                     break;
                 case kScanFieldL1:
-                    if (order_n && pkw) rc = TM_WORD_X("scan_word.cost.o16", kScanFieldL1, 32, 8);
+                    if (order_n && pkw == 16) rc = TM_WORD_X("scan_word.cost.o16", kScanFieldL1, 32, 16);
+                    else if (order_n && pkw) rc = TM_WORD_X("scan_word.cost.o16", kScanFieldL1, 32, 8);
                     else if (order_n) rc = TM_WORD_X("scan_word.cost", kScanFieldL1, 32, 0);
+                    else if (pkw == 16) rc = TM_WORD_X("scan_word.o16", kScanFieldL1, 0, 16);
                     else if (pkw) rc = TM_WORD_X("scan_word.o16", kScanFieldL1, 0, 8);
                     else rc = TM_WORD(kScanFieldL1);
                     break;
@@ -945,6 +990,41 @@ int run(Request &r) {
             else
                 rc = fin ? launch("line_pair_final", k_line_pair16<true>, lgrid, lblock, p.lds, r.stream, lp)
                          : launch("line_pair", k_line_pair16<false>, lgrid, lblock, p.lds, r.stream, lp);
+        } else if (p.bk) {
+            BracketArgs ba{};
+            ba.buf = index_path ? cidx : r.dist ? reinterpret_cast<int32_t *>(r.dist) : r.sq;
+            ba.dist = r.dist;
+            ba.sq = r.sq;
+            ba.lines = uint32_t(lines);
+            ba.n = n;
+            ba.inner = uint32_t(inner);
+            ba.div_inner = Div32::make(ba.inner);
+            ba.vox = uint32_t(vox);
+            ba.cstride = cstride;
+            ba.coords = coords;
+            ba.kbits = p.rbits;
+            ba.fcap = p.fcap;
+            const dim3 bgrid(uint32_t((lines + kBkLines - 1) / kBkLines));
+            if (order_n && a == 0 && bgrid.x == 2 * order_n) ba.order = r.ws + order_n;
+            // a wave per 4 segments of 16 lines, at most 16 waves
+            const uint32_t patches = (bk_segs(n, kBkSeg) + 3) / 4;
+            const dim3 bblock(kWave * std::min(patches, 16u));
+            const bool bpk = pkw == 16;
+#define TM_BK(NM, ...) launch(NM, k_line_bracket<__VA_ARGS__, kBkSeg>, bgrid, bblock, p.lds, r.stream, ba)
+            if (index_path)
+                rc = p.bk_key ? TM_BK("line_search_idx_final", kL2, kBkIndex, false, true)
+                              : TM_BK("line_search_idx_final", kL2, kBkIndex, false, false);
+            else if (r.metric == kLinf)
+                rc = fin ? (bpk ? TM_BK("cdt_line_final.i16", kLinf, kBkDist, true, false)
+                                : TM_BK("cdt_line_final", kLinf, kBkDist, false, false))
+                         : (bpk ? TM_BK("cdt_line.i16", kLinf, kBkField, true, false)
+                                : TM_BK("cdt_line", kLinf, kBkField, false, false));
+            else
+                rc = fin ? (bpk ? TM_BK("line_search_final.i16", kL2, kBkDist, true, false)
+                                : TM_BK("line_search_final", kL2, kBkDist, false, false))
+                         : (bpk ? TM_BK("line_search.i16", kL2, kBkField, true, false)
+                                : TM_BK("line_search", kL2, kBkField, false, false));
+#undef TM_BK
         } else if (p.l1scan) {
             LineSearchArgs la{};
             la.buf = r.sq;

@@ -1,0 +1,75 @@
+"""GPU parity of the bracketed column search (k_line_bracket): long lines of the
+first strided pass, and the index pass of 2-D inputs with more than 256 rows.
+Masks put every phase to work: near patches only (dense), far ones (a few discs),
+few site rows (one pixel), no background, one background block in a corner (the
+longest brackets), all background.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from gpu_util import announce, check_against_oracle, run_gpu
+from oracle import edt_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def masks(spatial, seed):
+    rng = np.random.default_rng(seed)
+    grid = np.ogrid[tuple(slice(0, n) for n in spatial)]
+    out = [rng.random(spatial) >= 0.3, rng.random(spatial) >= 0.004]
+    far = np.ones(spatial, bool)
+    for _ in range(6):
+        c = [rng.uniform(0, n) for n in spatial]
+        r = rng.uniform(0.02, 0.12) * min(spatial) + 1
+        far &= ~(sum((g - x) ** 2 for g, x in zip(grid, c)) <= r * r)
+    one = np.ones(spatial, bool)
+    one[tuple(rng.integers(0, n) for n in spatial)] = False
+    corner = np.ones(spatial, bool)
+    corner[tuple(slice(0, min(40, n)) for n in spatial)] = False
+    out += [far, one, np.ones(spatial, bool), corner, np.zeros(spatial, bool)]
+    return np.stack(out).astype(np.uint8)
+
+
+def names_of(fn):
+    from paper_2608_24738_amd import binding
+    binding.prof_enable(64)
+    try:
+        res = fn()
+        return res, {n for n, _ in binding.prof_read()}
+    finally:
+        binding.prof_enable(0)
+
+
+# rows at the rule's edge (640), one segment short and over, the last line a
+# 17th or 33rd of its group, the longest line; packed (wide multiples of 64) and not
+SHAPES = [(640, 17), (647, 33), (649, 128), (1024, 256), (2048, 31), (3, 645, 40)]
+
+
+@pytest.mark.parametrize("spatial", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_distances(spatial):
+    import torch
+
+    from paper_2608_24738_amd import binding
+    nd = len(spatial)
+    mask = masks(spatial, sum(spatial))
+    announce("bracket distances shape=%s" % (mask.shape,))
+    res, names = names_of(lambda: run_gpu(mask, nd, None, dist=True, idx=False, sq=True))
+    assert any(n.startswith("line_search") for n in names), names
+    check_against_oracle(mask, nd, None, res, edt_oracle.edt(mask, nd, None, nthreads=16))
+    x = torch.from_numpy(mask).cuda()
+    out = torch.empty(mask.shape, dtype=torch.int32, device=x.device)
+    _, names = names_of(lambda: (binding.tm_cdt(x, nd, 2, out), torch.cuda.synchronize()))
+    assert any(n.startswith("cdt_line") for n in names), names
+    assert np.array_equal(out.cpu().numpy(), edt_oracle.cdt(mask, nd, "chessboard", nthreads=16))
+
+
+# value and row in one key, and too large for one (11 bits of row beside 22 of value)
+@pytest.mark.parametrize("spatial", [(257, 48), (300, 33), (375, 500), (1024, 100), (1100, 1090), (2048, 40)],
+                         ids=lambda s: "%dx%d" % s)
+def test_indices(spatial):
+    mask = masks(spatial, sum(spatial) + 1)
+    announce("bracket indices shape=%s" % (mask.shape,))
+    res, names = names_of(lambda: run_gpu(mask, 2, None, dist=True, idx=True))
+    assert "line_search_idx_final" in names, names
+    check_against_oracle(mask, 2, None, res, edt_oracle.edt(mask, 2, None, nthreads=16))
+    only, _ = names_of(lambda: run_gpu(mask, 2, None, dist=False, idx=True))
+    assert np.array_equal(only["idx"], res["idx"])
