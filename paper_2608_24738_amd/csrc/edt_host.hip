@@ -836,21 +836,19 @@ int run(Request &r) {
                 rc = launch("order", k_order, dim3(1), dim3(kOrderThreads), 0, r.stream,
                             OrderArgs{r.ws, uint32_t(order_n)});
         } else if (nlast <= uint32_t(kSpan)) {
-            s.span_lines = uint32_t(kSpan) / nlast;
+            // whole lines of up to 1024 positions per wave, fewer on small
+            // inputs (at least four waves per SIMD, or 64 positions)
+            uint32_t span = uint32_t(kSpan);
+            while (span > uint32_t(kWave) && total / span < 4096) span /= 2;
+            s.span_lines = std::max(1u, span / nlast);
             const uint64_t waves = (uint64_t(s.lines) + s.span_lines - 1) / s.span_lines;
             const dim3 grid(uint32_t((waves + 3) / 4)), block(256);
-            const bool vec = mode != kScanFinal && nlast % 4 == 0 && kSpan % nlast == 0 &&
-                             uintptr_t(r.in) % 4 == 0 && uintptr_t(out) % 16 == 0;
-            switch (mode * 2 + (vec ? 1 : 0)) {
-                case kScanFieldInt * 2: rc = launch("scan_span", k_scan_span<kScanFieldInt, false>, grid, block, 0, r.stream, s); break;
-                case kScanFieldInt * 2 + 1: rc = launch("scan_span", k_scan_span<kScanFieldInt, true>, grid, block, 0, r.stream, s); break;
-                case kScanFieldL1 * 2: rc = launch("scan_span", k_scan_span<kScanFieldL1, false>, grid, block, 0, r.stream, s); break;
-                case kScanFieldL1 * 2 + 1: rc = launch("scan_span", k_scan_span<kScanFieldL1, true>, grid, block, 0, r.stream, s); break;
-                case kScanFieldFlt * 2: rc = launch("scan_span", k_scan_span<kScanFieldFlt, false>, grid, block, 0, r.stream, s); break;
-                case kScanFieldFlt * 2 + 1: rc = launch("scan_span", k_scan_span<kScanFieldFlt, true>, grid, block, 0, r.stream, s); break;
-                case kScanIndex * 2: rc = launch("scan_span", k_scan_span<kScanIndex, false>, grid, block, 0, r.stream, s); break;
-                case kScanIndex * 2 + 1: rc = launch("scan_span", k_scan_span<kScanIndex, true>, grid, block, 0, r.stream, s); break;
-                default: rc = launch("scan_span", k_scan_span<kScanFinal, false>, grid, block, 0, r.stream, s); break;
+            switch (mode) {
+                case kScanFieldInt: rc = launch("scan_span", k_scan_span<kScanFieldInt>, grid, block, 0, r.stream, s); break;
+                case kScanFieldL1: rc = launch("scan_span", k_scan_span<kScanFieldL1>, grid, block, 0, r.stream, s); break;
+                case kScanFieldFlt: rc = launch("scan_span", k_scan_span<kScanFieldFlt>, grid, block, 0, r.stream, s); break;
+                case kScanIndex: rc = launch("scan_span", k_scan_span<kScanIndex>, grid, block, 0, r.stream, s); break;
+                default: rc = launch("scan_span", k_scan_span<kScanFinal>, grid, block, 0, r.stream, s); break;
             }
         } else {
             s.span_lines = 1;

@@ -3,13 +3,8 @@
 // binary mask, so the lower envelope degenerates to "nearest zero in the
 // line").
 //
-// Each wavefront owns a span of up to 1024 consecutive mask bytes.  Lane l
-// holds the 16 positions 256k + 4l + j (k, j < 4), so every load instruction
-// of the wave reads 256 contiguous bytes and every store writes 1 KiB
-// contiguous.  The nearest zero on each side comes from per-lane 4-bit zero
-// masks, a wave-wide inclusive prefix-max (last zero so far) and suffix-min
-// (first zero from here), and carries across the four groups.  Ties between
-// an equally distant left and right zero go to the left (smaller) one.
+// Ties between an equally distant left and right zero go to the left
+// (smaller) one.
 #pragma once
 
 #include "edt_common.h"
@@ -47,8 +42,10 @@ struct ScanArgs {
 
 constexpr int kBig = 0x3fffffff;
 
-// Left/right zero candidates for the 16 positions a lane holds in one 1024-
-// position chunk.  zb[k] bit j marks a zero at chunk position 256k + 4l + j.
+// Left/right zero candidates for the 16 positions 256k + 4l + j (k, j < 4) that
+// lane l holds in one 1024-position chunk (k_scan_long): per-lane 4-bit zero
+// masks, a wave-wide prefix maximum (last zero so far) and suffix minimum
+// (first zero from here), and carries across the four groups.  zb[k] bit j marks a zero at chunk position 256k + 4l + j.
 // cl / cr: last zero before / first zero after the chunk (chunk-relative,
 // -kBig / kBig when none).  Outputs chunk-relative candidates (-kBig / kBig
 // when none).
@@ -100,135 +97,129 @@ __device__ inline void chunk_candidates(const uint32_t zb[4], int cl, int cr, in
 }
 
 // Zero masks of one chunk: positions >= valid read as foreground.
-template <bool VEC>
 __device__ inline void load_zero_bits(const uint8_t *p, int valid, int lane, uint32_t zb[4]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        int base = 256 * k + 4 * lane;
+        const int base = 256 * k + 4 * lane;
         uint32_t bits = 0;
-        if (VEC) {
-            uint32_t word = *reinterpret_cast<const uint32_t *>(p + base);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bits |= ((word >> (8 * j)) & 0xffu) == 0 ? (1u << j) : 0u;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (base + j < valid && p[base + j] == 0) bits |= 1u << j;
-        }
+        for (int j = 0; j < 4; ++j)
+            if (base + j < valid && p[base + j] == 0) bits |= 1u << j;
         zb[k] = bits;
     }
 }
 
-// Writes the results of four consecutive positions (x0 .. x0+3 of one line,
-// line-relative; y[j] = line-relative zero or -1) for line `gline`.
-template <int MODE, bool VEC>
-__device__ inline void scan_store4(const ScanArgs &a, uint32_t gline, int x0, const int y[4],
-                                   int count) {
+// Writes the result of position x of line `gline` (y: line-relative zero or -1).
+template <int MODE>
+__device__ inline void scan_store(const ScanArgs &a, uint32_t gline, int x, int y) {
     const uint64_t lbase = uint64_t(gline) * a.n;  // batch-flat start of the line
     if (MODE == kScanFieldInt || MODE == kScanFieldL1) {
-        int32_t v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int d = x0 + j - y[j];
-            if (MODE == kScanFieldL1) d = d < 0 ? -d : d;
-            v[j] = y[j] >= 0 ? (MODE == kScanFieldL1 ? d : d * d) : kInfI;
-        }
-        int32_t *o = a.field_i + lbase + x0;
-        if (VEC) {
-            *reinterpret_cast<int4 *>(o) = make_int4(v[0], v[1], v[2], v[3]);
-        } else {
-            for (int j = 0; j < count; ++j) o[j] = v[j];
-        }
+        const int d = x - y;
+        a.field_i[lbase + x] = y < 0 ? kInfI : MODE == kScanFieldL1 ? abs(d) : d * d;
     } else if (MODE == kScanFieldFlt) {
-        float v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            double d = double(x0 + j - y[j]);
-            v[j] = y[j] >= 0 ? float(a.w * (d * d)) : __builtin_inff();
-        }
-        float *o = a.field_f + lbase + x0;
-        if (VEC) {
-            *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-            for (int j = 0; j < count; ++j) o[j] = v[j];
-        }
+        const double d = double(x - y);
+        a.field_f[lbase + x] = y >= 0 ? float(a.w * (d * d)) : __builtin_inff();
     } else if (MODE == kScanIndex) {
-        uint32_t s = a.div_lps.div(gline);
-        uint32_t lline = gline - s * a.lps;
-        uint64_t local = uint64_t(lline) * a.n;
-        int32_t v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = y[j] >= 0 ? int32_t(local + y[j]) : kNoIdx;
-        int32_t *o = a.idx + uint64_t(s) * a.cstride + local + x0;
-        if (VEC) {
-            *reinterpret_cast<int4 *>(o) = make_int4(v[0], v[1], v[2], v[3]);
-        } else {
-            for (int j = 0; j < count; ++j) o[j] = v[j];
-        }
+        const uint32_t s = a.div_lps.div(gline);
+        const uint64_t local = uint64_t(gline - s * a.lps) * a.n;
+        a.idx[uint64_t(s) * a.cstride + local + x] = y >= 0 ? int32_t(local + y) : kNoIdx;
     } else {  // kScanFinal: rank 1, the line is the whole sample
-        for (int j = 0; j < count; ++j) {
-            int x = x0 + j;
-            double d = y[j] >= 0 ? double(x - y[j]) : double(x + 1);  // virtual zero at -1
-            if (a.dist) a.dist[lbase + x] = float(sqrt(a.w * (d * d)));
-            if (a.sq) {
-                int64_t di = y[j] >= 0 ? int64_t(x - y[j]) : int64_t(x + 1);
-                a.sq[lbase + x] = int32_t(di * di);
-            }
-            if (a.idx) a.idx[lbase + x] = y[j] >= 0 ? y[j] : -1;
+        const double d = y >= 0 ? double(x - y) : double(x + 1);  // virtual zero at -1
+        if (a.dist) a.dist[lbase + x] = float(sqrt(a.w * (d * d)));
+        if (a.sq) {
+            const int64_t di = y >= 0 ? int64_t(x - y) : int64_t(x + 1);
+            a.sq[lbase + x] = int32_t(di * di);
         }
+        if (a.idx) a.idx[lbase + x] = y >= 0 ? y : -1;
     }
 }
 
-// Lines of length n <= 1024: each wavefront scans `span_lines` whole lines.
-template <int MODE, bool VEC>
+// Lines of length n <= 1024: each wavefront scans `span_lines` whole lines, at
+// most 1024 positions, lane l holding positions 64 k + l.  A chunk's zeros are
+// one ballot; the distance to the nearest zero on each side comes from the
+// ballot's bits up to and from the lane, or from the last zero before and the
+// first one after the chunk (the same for all lanes), and counts when it stays in
+// the lane's line.
+// Loads read 64 and stores write 256 contiguous bytes whatever the line length.
+//
+// Bound by VALU issue (about 45 instructions per position):
+// 2 x 155 x 240 x 237 in 34 us, against 41 us with 16 positions per lane in
+// runs of four (per-byte loads and stores 16 bytes apart on odd lengths);
+// 3 x 64 x 213 in 4.1 us, against 7.4 us.
+constexpr int kSpanChunks = kSpan / kWave;
+
+template <int MODE>
 __global__ void __launch_bounds__(256) k_scan_span(ScanArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     const uint64_t line0 = uint64_t(wave) * a.span_lines;
     if (line0 >= a.lines) return;  // whole wavefront exits together
     const uint32_t nl = uint32_t(min<uint64_t>(a.span_lines, a.lines - line0));
-    const int valid = int(nl * a.n);
+    const int valid = int(__builtin_amdgcn_readfirstlane(nl * a.n));
     const uint8_t *src = a.in + line0 * a.n;
-    const bool full = VEC && valid == kSpan;
 
-    uint32_t zb[4];
-    if (full) load_zero_bits<true>(src, valid, lane, zb);
-    else load_zero_bits<false>(src, valid, lane, zb);
-    int left[4][4], right[4][4];
-    chunk_candidates(zb, -kBig, kBig, lane, left, right);
-
+    uint8_t v[kSpanChunks];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int p0 = 256 * k + 4 * lane;  // span position of the group's first element
-        if (p0 >= valid) continue;
-        // With n % 4 == 0 (vector path) the four positions share one line.
-        int y[4];
-        uint32_t line_of[4];
-        int xs[4];
+    for (int k = 0; k < kSpanChunks; ++k) {
+        if (64 * k >= valid) break;
+        v[k] = src[min(64 * k + lane, valid - 1)];
+    }
+    // zeros of each chunk, and the first zero after it
+    uint64_t zb[kSpanChunks];
+    int next[kSpanChunks];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int p = p0 + j;
-            uint32_t l = a.div_n.div(uint32_t(p));
-            int ls = int(l * a.n);
-            int le = ls + int(a.n);
-            bool hl = left[k][j] >= ls;
-            bool hr = right[k][j] < le && right[k][j] < valid;
-            int yy = -1;
-            if (hl && (!hr || p - left[k][j] <= right[k][j] - p)) yy = left[k][j] - ls;
-            else if (hr) yy = right[k][j] - ls;
-            y[j] = yy;
-            line_of[j] = l;
-            xs[j] = p - ls;
-        }
-        if (full) {
-            scan_store4<MODE, true>(a, uint32_t(line0) + line_of[0], xs[0], y, 4);
-        } else {
-            for (int j = 0; j < 4; ++j) {
-                if (p0 + j >= valid) break;
-                int yy[4] = {y[j], -1, -1, -1};
-                scan_store4<MODE, false>(a, uint32_t(line0) + line_of[j], xs[j], yy, 1);
+    for (int k = 0; k < kSpanChunks; ++k) zb[k] = 64 * k < valid ? __ballot(64 * k + lane < valid && v[k] == 0) : 0;
+    int nz = kBig;
+#pragma unroll
+    for (int k = kSpanChunks - 1; k >= 0; --k) {
+        next[k] = nz;
+        if (zb[k]) nz = 64 * k + __builtin_ctzll(zb[k]);
+    }
+    // index carrier: the wave's lines lie in one sample (else per lane)
+    uint32_t smp = 0, local = 0;
+    bool split = false;
+    if constexpr (MODE == kScanIndex) {
+        smp = a.div_lps.div(uint32_t(line0));
+        local = uint32_t(line0) - smp * a.lps;
+        split = local + nl > a.lps;
+        local *= a.n;
+    }
+    constexpr uint32_t kFar = 1u << 16;                         // no zero in the line
+    const uint32_t rem = uint32_t(kWave) % a.n;
+    uint32_t x = uint32_t(lane) % a.n;                          // position in the line
+    int last = -kBig;                                           // last zero before the chunk
+#pragma unroll
+    for (int k = 0; k < kSpanChunks; ++k) {
+        if (64 * k >= valid) break;
+        const int p = 64 * k + lane;
+        // distances to the last zero at or before p and to the first one from p
+        // (all ones from an empty half word survives the "or" with 32)
+        const uint64_t lo = zb[k] << (kWave - 1 - lane), hi = zb[k] >> lane;
+        const uint32_t lh = uint32_t(lo >> 32), ll = uint32_t(lo), hh = uint32_t(hi >> 32), hl = uint32_t(hi);
+        auto clz = [](uint32_t w) { return w ? uint32_t(__builtin_clz(w)) : ~0u; };
+        auto ctz = [](uint32_t w) { return w ? uint32_t(__builtin_ctz(w)) : ~0u; };
+        uint32_t dl = min(clz(lh), clz(ll) | 32u);
+        uint32_t dr = min(ctz(hl), ctz(hh) | 32u);
+        dl = min(dl, uint32_t(p - last));
+        dr = min(dr, uint32_t(next[k] - p));
+        if (zb[k]) last = 64 * k + 63 - __builtin_clzll(zb[k]);
+        dl = dl <= x ? dl : kFar;
+        dr = dr < a.n - x ? dr : kFar;
+        const uint32_t d = min(dl, dr);
+        if (p < valid) {
+            if constexpr (MODE == kScanFieldInt || MODE == kScanFieldL1) {
+                a.field_i[line0 * a.n + uint32_t(p)] =
+                    d >= kFar ? kInfI : MODE == kScanFieldL1 ? int32_t(d) : int32_t(__umul24(d, d));
+            } else if (MODE == kScanIndex && !split) {
+                a.idx[uint64_t(smp) * a.cstride + local + uint32_t(p)] =
+                    d >= kFar ? kNoIdx : int32_t(local) + (dl <= dr ? p - int(dl) : p + int(dr));
+            } else {
+                scan_store<MODE>(a, uint32_t(line0) + a.div_n.div(uint32_t(p)), int(x),
+                                 d >= kFar ? -1 : dl <= dr ? int(x - dl) : int(x + dr));
             }
         }
+        x += rem;
+        x = min(x, x - a.n);                                    // (unsigned: less the line length if past it)
     }
 }
 
@@ -267,7 +258,7 @@ __global__ void __launch_bounds__(64) k_scan_long(ScanArgs a) {
     for (int c = chunks - 1; c >= 0; --c) {
         const int valid = min(kSpan, n - c * kSpan);
         uint32_t zb[4];
-        load_zero_bits<false>(src + c * kSpan, valid, lane, zb);
+        load_zero_bits(src + c * kSpan, valid, lane, zb);
         int m = kBig;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -282,7 +273,7 @@ __global__ void __launch_bounds__(64) k_scan_long(ScanArgs a) {
         const int valid = min(kSpan, n - c * kSpan);
         const int off = c * kSpan;
         uint32_t zb[4];
-        load_zero_bits<false>(src + off, valid, lane, zb);
+        load_zero_bits(src + off, valid, lane, zb);
         const int cl = last == -kBig ? -kBig : last - off;
         const int nxt = c + 1 < chunks ? int(*scan_slot<MODE>(a, gline, (c + 1) * kSpan)) : kBig;
         const int cr = nxt == kBig ? kBig : nxt - off;
@@ -307,8 +298,7 @@ __global__ void __launch_bounds__(64) k_scan_long(ScanArgs a) {
                 int yy = -1;
                 if (hl && (!hr || p - l <= r - p)) yy = l + off;
                 else if (hr) yy = r + off;
-                int ys[4] = {yy, -1, -1, -1};
-                scan_store4<MODE, false>(a, gline, p + off, ys, 1);
+                scan_store<MODE>(a, gline, p + off, yy);
             }
         }
     }
