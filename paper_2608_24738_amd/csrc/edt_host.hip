@@ -232,6 +232,7 @@ struct FhPlan {
     bool lng;        // index carrier, envelope in the line's own storage (k_fh_long)
     bool l1long;     // taxicab, two running minima in place (k_cdt_l1_long)
     bool l1scan;     // taxicab, whole lines in LDS, prefix and suffix minima (k_cdt_l1_scan)
+    bool l1rag;      //   with lines of any stride and alignment
     bool lp16;       // 16 lines per workgroup, two per packed 16-bit word (k_line_pair16)
     int bk;          // bracketed search (k_line_bracket): rows per segment, 0 = not
     bool bk_key;     //   index carrier: value and row in one key
@@ -456,13 +457,12 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
             }
             if (r.metric == kLinf && plan_bracket(p, r, a, total, false)) continue;
             const uint64_t cmax = r.metric == kL1 ? vmax + n + 4 : std::max<uint64_t>(vmax, n + 4);
-            // taxicab lines whose 8-line groups share rows: prefix and suffix
-            // minima, no search
+            // taxicab whole lines: prefix and suffix minima, no search
             const void *cfield = r.sq;
-            if (r.metric == kL1 && inner % kL1Lines == 0 && n <= kL1MaxN && cmax < (uint64_t(1) << 29) &&
-                l1scan_lds(n) + 1024 <= kLdsBytes && total / n / kL1Lines < (uint64_t(1) << 31) &&
-                uintptr_t(cfield) % 16 == 0) {
+            if (r.metric == kL1 && n <= kL1MaxN && cmax < (uint64_t(1) << 29) && l1scan_lds(n) + 1024 <= kLdsBytes &&
+                total / n + kL1Lines < (uint64_t(1) << 32)) {
                 p.l1scan = true;
+                p.l1rag = inner % kL1Lines != 0 || uintptr_t(cfield) % 16 != 0;
                 p.lds = l1scan_lds(n);
                 continue;
             }
@@ -794,7 +794,7 @@ int run(Request &r) {
                 !fh[nd - 2].tiled16) {
                 const FhPlan &p1 = fh[nd - 2];
                 if ((mode == kScanFieldInt && p1.lp16) || (mode == kScanFieldL1 && p1.bk)) pkw = 16;
-                else if ((mode == kScanFieldInt || mode == kScanFieldL1) && !p1.lp16 && (p1.ls_lpw == 8 || p1.l1scan))
+                else if ((mode == kScanFieldInt || mode == kScanFieldL1) && !p1.lp16 && (p1.ls_lpw == 8 || (p1.l1scan && !p1.l1rag)))
                     pkw = 8;
             }
             ws.n1 = nd >= 2 ? r.shape[nd - 2] : 1;
@@ -1030,16 +1030,20 @@ int run(Request &r) {
             la.n = n;
             la.inner = uint32_t(inner);
             la.div_inner = Div32::make(la.inner);
-            const dim3 lgrid(uint32_t(lines / kL1Lines)), lblock(kWave * kL1Lines);
+            const dim3 lgrid(uint32_t((lines + kL1Lines - 1) / kL1Lines)), lblock(kWave * kL1Lines);
             const bool lpk = pkw == 8 && a == nd - 2;
             const char *nm = fin ? (lpk ? "cdt_l1_scan_final.i16" : "cdt_l1_scan_final")
                                  : (lpk ? "cdt_l1_scan.i16" : "cdt_l1_scan");
-            // 16 rows per lane up to 1024 rows, else 36
-            const bool r16 = n <= uint32_t(16 * kWave);
-#define TM_L1S(F, PK)                                                                                   \
-    (r16 ? launch(nm, k_cdt_l1_scan<F, PK, 16>, lgrid, lblock, p.lds, r.stream, la)                      \
-         : launch(nm, k_cdt_l1_scan<F, PK, 36>, lgrid, lblock, p.lds, r.stream, la))
-            rc = lpk ? (fin ? TM_L1S(true, true) : TM_L1S(false, true)) : (fin ? TM_L1S(true, false) : TM_L1S(false, false));
+            // rows per lane: the fewest that hold the line
+#define TM_L1S(F, PK, RG)                                                                                \
+    (n <= 4u * kWave    ? launch(nm, k_cdt_l1_scan<F, PK, 4, RG>, lgrid, lblock, p.lds, r.stream, la)     \
+     : n <= 8u * kWave  ? launch(nm, k_cdt_l1_scan<F, PK, 8, RG>, lgrid, lblock, p.lds, r.stream, la)     \
+     : n <= 12u * kWave ? launch(nm, k_cdt_l1_scan<F, PK, 12, RG>, lgrid, lblock, p.lds, r.stream, la)    \
+     : n <= 16u * kWave ? launch(nm, k_cdt_l1_scan<F, PK, 16, RG>, lgrid, lblock, p.lds, r.stream, la)    \
+                        : launch(nm, k_cdt_l1_scan<F, PK, 36, RG>, lgrid, lblock, p.lds, r.stream, la))
+            if (p.l1rag) rc = fin ? TM_L1S(true, false, true) : TM_L1S(false, false, true);
+            else if (lpk) rc = fin ? TM_L1S(true, true, false) : TM_L1S(false, true, false);
+            else rc = fin ? TM_L1S(true, false, false) : TM_L1S(false, false, false);
 #undef TM_L1S
         } else if (p.ls_lpw) {
             LineSearchArgs la{};
