@@ -202,10 +202,15 @@ int validate(const uint8_t *in, int ndim, const int64_t *shape, int64_t batch,
 // per workgroup) is faster.
 constexpr uint64_t kPairMinLines = 256 * kPairLines;
 
-// Workgroups of 16 lines below which the packed line pass leaves compute
-// units idle (two workgroups of 16 waves fill one): fewer lines take the
-// whole-line search with 8 lines per workgroup.
-constexpr uint64_t kLpMinGroups = 512;
+// Groups of 16 lines below which the packed line pass leaves compute units
+// idle, and fewer lines take the whole-line search with 8 lines per workgroup
+// (pass, us, whole-line -> packed: 8 x 512^2, 256 groups, balls 33 -> 24, discs 32
+// -> 27; 8 x 256^2, 128 groups, 8.4 -> 12.5).  With one element per lane (lines
+// of any stride) the line lies higher: 16 x 375 x 500, 500 groups, 28 -> 26 and
+// 32 -> 31, but 8 x 500 x 803, 402 groups, discs 53 -> 72, 16 x 200 x 333, 333
+// groups, 12 -> 12 and 14 -> 20.
+constexpr uint64_t kLpMinGroups = 256;
+constexpr uint64_t kLpMinGroupsRag = 512;
 
 // Rows from which a distance pass takes the bracketed search instead of the
 // whole-line windowed one, whose work grows with the distances.  Measured
@@ -234,6 +239,7 @@ struct FhPlan {
     bool l1scan;     // taxicab, whole lines in LDS, prefix and suffix minima (k_cdt_l1_scan)
     bool l1rag;      //   with lines of any stride and alignment
     bool lp16;       // 16 lines per workgroup, two per packed 16-bit word (k_line_pair16)
+    bool lprag;      //   the same with lines of any length, stride and alignment
     int bk;          // bracketed search (k_line_bracket): rows per segment, 0 = not
     bool bk_key;     //   index carrier: value and row in one key
     uint32_t fcap;   //   value of rows without sites in a key
@@ -519,19 +525,21 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
                 continue;
             }
         }
-        // Unit sampling without indices, lines of up to 512 rows (a multiple
-        // of 16) whose 16 neighbours along the later axes are adjacent in
-        // memory: 16 lines per workgroup, two per packed 16-bit word, while
-        // that leaves at least two workgroups per compute unit and every
-        // exact candidate stays in int32.
-        if (!index_path && r.unit && n <= kLpMaxN && n % 16 == 0) {
+        // Unit sampling without indices, lines of up to 512 rows: 16 lines per
+        // workgroup, two per packed 16-bit word, while that fills the chip and
+        // every exact candidate stays in int32.  Vector loads and stores where lines of a multiple of 16 rows
+        // have their 16 neighbours adjacent in memory (lp16), else one element
+        // per lane (lprag).
+        if (!index_path && r.unit && n <= kLpMaxN) {
             uint64_t inner = 1;
             for (int b = a + 1; b < nd; ++b) inner *= r.shape[b];
-            const uint64_t groups = total / n / kLpLines;
+            const uint64_t groups = (total / n + kLpLines - 1) / kLpLines;
             const void *field = r.dist ? static_cast<const void *>(r.dist) : static_cast<const void *>(r.sq);
-            if (inner % kLpLines == 0 && groups >= kLpMinGroups && groups < (uint64_t(1) << 31) &&
-                fmax + uint64_t(n - 1) * (n - 1) < uint64_t(kInfI) && uintptr_t(field) % 16 == 0) {
-                p.lp16 = true;
+            const bool rag = n % 16 != 0 || inner % kLpLines != 0 || uintptr_t(field) % 16 != 0;
+            if (groups >= (rag ? kLpMinGroupsRag : kLpMinGroups) && total / n + kLpLines < (uint64_t(1) << 32) &&
+                fmax + uint64_t(n - 1) * (n - 1) < uint64_t(kInfI)) {
+                p.lp16 = !rag;
+                p.lprag = rag;
                 p.lds = lpair_lds(n);
                 continue;
             }
@@ -612,7 +620,7 @@ OrderPlan order_groups(const Request &r, const FhPlan *fh, uint64_t total) {
     if (r.ndim != 2 || !r.unit || r.big || r.idx || r.sgn) return {0, 0};
     // k_line_search orders units of four groups of 8 lines (32 columns)
     const uint32_t width = (fh[0].lp16 && r.metric == kL2) ? uint32_t(kLpLines)
-                           : (!fh[0].tiled16 && !fh[0].l1long && (fh[0].ls_lpw == 8 || fh[0].bk)) ? 32u : 0u;
+                           : (!fh[0].tiled16 && !fh[0].l1long && !fh[0].lprag && (fh[0].ls_lpw == 8 || fh[0].bk)) ? 32u : 0u;
     if (!width) return {0, 0};
     const uint32_t n0 = r.shape[0], nlast = r.shape[1];
     if (nlast % kWave != 0 || nlast > uint32_t(kWave * kWave) || nlast / width > 256) return {0, 0};
@@ -791,7 +799,7 @@ int run(Request &r) {
             // packed field: the next pass takes it, and every wave's rows pair
             // up (an even number of them) inside one block of that axis's rows
             if (nd >= 2 && wsh.lpw % 2 == 0 && r.shape[nd - 2] % wsh.lpw == 0 && !fh[nd - 2].l1long &&
-                !fh[nd - 2].tiled16) {
+                !fh[nd - 2].tiled16 && !fh[nd - 2].lprag) {
                 const FhPlan &p1 = fh[nd - 2];
                 if ((mode == kScanFieldInt && p1.lp16) || (mode == kScanFieldL1 && p1.bk)) pkw = 16;
                 else if ((mode == kScanFieldInt || mode == kScanFieldL1) && !p1.lp16 && (p1.ls_lpw == 8 || (p1.l1scan && !p1.l1rag)))
@@ -965,7 +973,7 @@ int run(Request &r) {
                     rc = fin ? launch(nm, k_tile_pair<true, false, 16>, tgrid, tblock, p.lds, r.stream, tg)
                              : launch(nm, k_tile_pair<false, false, 16>, tgrid, tblock, p.lds, r.stream, tg);
             }
-        } else if (p.lp16) {
+        } else if (p.lp16 || p.lprag) {
             LinePairArgs lp{};
             lp.buf = r.dist ? reinterpret_cast<int32_t *>(r.dist) : r.sq;
             lp.dist = r.dist;
@@ -974,15 +982,20 @@ int run(Request &r) {
             lp.n = n;
             lp.inner = uint32_t(inner);
             lp.div_inner = Div32::make(lp.inner);
-            lp.mult = plane_stride(uint32_t((lines / kLpLines) & ~uint64_t(31)) / 4u);
+            lp.mult = plane_stride(uint32_t(((lines + kLpLines - 1) / kLpLines) & ~uint64_t(31)) / 4u);
             lp.ndim = nd;
             for (int b = 0; b < nd; ++b) {
                 lp.shape[b] = r.shape[b];
                 lp.wall[b] = r.w[b];
             }
-            const dim3 lgrid(uint32_t(lines / kLpLines)), lblock(kPsThreads);
+            // a wave per two patches of 16 rows, at most 16
+            const uint32_t lwaves = std::min(16u, ((n + 15) / 16 + 1) / 2);
+            const dim3 lgrid(uint32_t((lines + kLpLines - 1) / kLpLines)), lblock(kWave * lwaves);
             if (order_n && a == 0 && lgrid.x == order_n) lp.order = r.ws + order_n;
-            if (pkw == 16 && a == nd - 2)
+            if (p.lprag)
+                rc = fin ? launch("line_search_pair_final", k_line_pair16<true, false, true>, lgrid, lblock, p.lds, r.stream, lp)
+                         : launch("line_search_pair", k_line_pair16<false, false, true>, lgrid, lblock, p.lds, r.stream, lp);
+            else if (pkw == 16 && a == nd - 2)
                 rc = fin ? launch("line_pair_final.i16", k_line_pair16<true, true>, lgrid, lblock, p.lds, r.stream, lp)
                          : launch("line_pair.i16", k_line_pair16<false, true>, lgrid, lblock, p.lds, r.stream, lp);
             else

@@ -16,6 +16,11 @@
 // that row, so a result below 0xfffe is exact; a wave with any result of
 // 0xfffe or more (a distance of at least 256, or no site) searches its patch
 // again in 32-bit on the exact copy.
+// A workgroup has one wave per two patches: patches differ in work, and waves
+// that find none left hold their slots until the last one ends (2 x 256^3 balls,
+// 16 patches: the two passes 74 + 78 us on 16 waves, 52 + 53 us on 8; ragged
+// 2 x 155 x 240 x 237 balls 58 + 65 against 37 + 41 us, and 63 + 80 us with the
+// whole-line search).
 // Workgroups whose lines hold at most kLpDirect rows with any site take, for
 // every element, the minimum over those rows directly from the exact copy:
 // on such lines the distances can reach the line length.
@@ -59,10 +64,16 @@ struct LinePairArgs {
 // last rows, where a clamped read only overestimates).  Squared distances
 // from 256 on are clamped to 0xffff: such candidates, and the search's end,
 // only matter to results the caller redoes exactly.
+// RAG: queries past the line's end search nothing (n is any number of rows).
+template <bool RAG>
 __device__ __forceinline__ void lp_search(const uint32_t *code, int n, int q, int word, u16x2 &bA, u16x2 &bB) {
-    const int o = (q + kLpG) * kLpRS + word;
+    const int o = ((RAG ? min(q, n - 1) : q) + kLpG) * kLpRS + word;
     bA = as_pair(code[o]);
     bB = as_pair(code[o + kLpRS]);
+    if (RAG) {
+        if (q >= n) bA = splat(0);
+        if (q + 1 >= n) bB = splat(0);
+    }
     constexpr uint32_t kStep = 4 * kLpRS * 4;       // four rows, in bytes
     const uint32_t bu = lds_byte_addr(code);
     const uint32_t lo_min = bu + 4 * word, hi_max = bu + 4 * ((n - 1 + kLpG) * kLpRS + word);
@@ -109,6 +120,7 @@ __device__ __forceinline__ void lp_search(const uint32_t *code, int n, int q, in
 // distances stay below 2^31 on this path, host eligibility, so kInfI plus
 // any squared distance stays above every real candidate in uint32).  Reads
 // clamp to the line's first and last rows.
+template <bool RAG>
 __device__ __forceinline__ void lp_search32(const int32_t *exact, int n, int q, int l, uint32_t (&best)[4]) {
     auto row2 = [&](int r) {
         const int rr = min(max(r, 0), n - 1);
@@ -117,6 +129,10 @@ __device__ __forceinline__ void lp_search32(const int32_t *exact, int n, int q, 
     };
     const uint2 a0 = row2(q), a1 = row2(q + 1);
     best[0] = a0.x; best[1] = a0.y; best[2] = a1.x; best[3] = a1.y;
+    if (RAG) {
+        if (q >= n) best[0] = best[1] = 0;
+        if (q + 1 >= n) best[2] = best[3] = 0;
+    }
     for (int d = 1; d < n; d += 4) {
         const uint32_t dd = uint32_t(d) * uint32_t(d);
         const uint32_t m = max(max(best[0], best[1]), max(best[2], best[3]));
@@ -144,8 +160,14 @@ __device__ __forceinline__ void lp_search32(const int32_t *exact, int n, int q, 
 // no site) are the 16-bit pairs in the 32 bytes at word 8 (r & 1) of row r / 2;
 // the exact copy takes d * d.  Only this workgroup reads or writes its strip,
 // and it writes only after staging all of it.
-template <bool FINAL, bool PK = false>
+// RAG: any line length up to kLpMaxN, any stride and alignment; a group's 16
+// lines may lie in two blocks of rows, and the last group may be partial.  One
+// element per lane on the way in; on the way out a lane's two lines go in one
+// 8-byte store (aligned to 4) where they are adjacent.
+template <bool FINAL, bool PK = false, bool RAG = false>
 __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
+    static_assert(!(PK && RAG), "packed strips are whole groups of lines");
+    typedef int int2u __attribute__((ext_vector_type(2), aligned(4)));
     extern __shared__ __attribute__((aligned(16))) uint32_t lp_lds[];
     const int n = int(a.n);
     uint32_t *const code = lp_lds;                                           // [n + 2G][kLpRS]
@@ -154,6 +176,9 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
     __shared__ uint32_t claim;
     __shared__ uint32_t site_rows;        // rows of the workgroup holding a site
     __shared__ uint16_t site_row[kLpDirect];
+    __shared__ uint64_t line_base[kLpLines];      // RAG: row 0 of each line
+    __shared__ uint32_t line_i[kLpLines];         // RAG: its position along the later axes
+    const int nthreads = int(blockDim.x);
     const int t = threadIdx.x;
     const int lane = t & (kWave - 1);
 
@@ -174,23 +199,55 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
         const uint32_t sets = (gridDim.x & ~31u) / 4u;
         g = uint32_t((uint64_t(g >> 2) * a.mult) % sets) * 4u + (g & 3u);
     }
-    const uint32_t L0 = g * uint32_t(kLpLines);
+    // line 0 of the group; RAG: the line this thread stages (past the last: it again)
+    const uint32_t G0 = g * uint32_t(kLpLines);
+    const uint32_t L0 = RAG ? min(G0 + uint32_t(t % kLpLines), a.lines - 1u) : G0;
     const uint32_t o = a.div_inner.div(L0);
-    const uint32_t i0 = L0 - o * a.inner;                                   // position of line 0
-    const uint64_t base = uint64_t(o) * a.n * a.inner + i0;                 // row 0 of line 0
+    const uint32_t i0 = L0 - o * a.inner;                                   // its position
+    const uint64_t base = uint64_t(o) * a.n * a.inner + i0;                 // its row 0
+    const uint32_t nlive = RAG ? min(a.lines - G0, uint32_t(kLpLines)) : uint32_t(kLpLines);
+    if (RAG && t < kLpLines) {
+        line_base[t] = base;
+        line_i[t] = i0;
+    }
 
     // ---- stage: thread t holds lines 8 (t & 1) .. + 7 of rows t / 2, t / 2 + 512, ...
     if (t == 0) {
         claim = 0;
         site_rows = 0;
     }
-    for (int k = t; k < 2 * kLpG * kLpRS; k += kPsThreads) {
+    for (int k = t; k < 2 * kLpG * kLpRS; k += nthreads) {
         const int row = k / kLpRS, col = k % kLpRS;
         code[(row < kLpG ? row : n + row) * kLpRS + col] = 0xffffffffu;
     }
-    for (int k = t; k < kLpLut; k += kPsThreads) lut[k] = __builtin_bit_cast(uint32_t, sqrt_rn_int(uint32_t(k)));
+    for (int k = t; k < kLpLut; k += nthreads) lut[k] = __builtin_bit_cast(uint32_t, sqrt_rn_int(uint32_t(k)));
     __syncthreads();
-    for (int r = t >> 1; r < n; r += kPsThreads / 2) {
+    if constexpr (RAG) {
+        constexpr int SB = 8;
+        const int STEP = nthreads / kLpLines;    // rows in flight per thread
+        const int j = t % kLpLines;
+        uint16_t *const half = reinterpret_cast<uint16_t *>(code);
+        for (int r0 = t / kLpLines; r0 < n; r0 += SB * STEP) {
+            int32_t v[SB];
+#pragma unroll
+            for (int k = 0; k < SB; ++k) v[k] = a.buf[base + uint64_t(min(r0 + k * STEP, n - 1)) * a.inner];
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+                const int r = r0 + k * STEP;
+                const bool site = r < n && v[k] != kInfI;
+                if (r < n) {
+                    exact[r * kLpLines + j] = v[k];
+                    half[(r + kLpG) * 2 * kLpRS + j] = v[k] == kInfI ? uint16_t(0xffff) : uint16_t(min(uint32_t(v[k]), 0xfffeu));
+                }
+                const uint64_t b = __ballot(site) >> (lane & ~(kLpLines - 1));
+                if (j == 0 && (b & 0xffffu)) {
+                    const uint32_t x = atomicAdd(&site_rows, 1u);
+                    if (x < uint32_t(kLpDirect)) site_row[x] = uint16_t(r);
+                }
+            }
+        }
+    }
+    for (int r = t >> 1; r < (RAG ? 0 : n); r += nthreads / 2) {
         const int h = t & 1;
         int32_t v[8];
         if constexpr (PK) {
@@ -232,13 +289,14 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
 
     // value of element (row q, line l) for the outputs
     auto emit = [&](int q, int l, uint32_t v, bool none) -> void {
-        const uint64_t e = base + uint64_t(q) * a.inner + uint32_t(l);
+        if (RAG && (q >= n || uint32_t(l) >= nlive)) return;
+        const uint64_t e = (RAG ? line_base[l] : base + uint32_t(l)) + uint64_t(q) * a.inner;
         if (!FINAL) {
             a.buf[e] = none ? kInfI : int32_t(v);
             return;
         }
         int64_t d2 = int64_t(v);
-        if (none) d2 = virtual_sq<int64_t>(q, i0 + uint32_t(l), a.ndim, a.shape, a.wall);   // no background
+        if (none) d2 = virtual_sq<int64_t>(q, RAG ? line_i[l] : i0 + uint32_t(l), a.ndim, a.shape, a.wall);   // no background
         const float dv = d2 < kLpLut ? __builtin_bit_cast(float, lut[d2])
                          : d2 < (int64_t(1) << 24) ? sqrt_rn_int(uint32_t(d2))
                                                    : float(sqrt(double(d2)));
@@ -247,7 +305,7 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
     };
     if (nsites <= uint32_t(kLpDirect)) {
         // few site rows: the minimum over them, for every element
-        for (int k = t; k < n * kLpLines; k += kPsThreads) {
+        for (int k = t; k < n * kLpLines; k += nthreads) {
             const int q = k / kLpLines, l = k % kLpLines;
             uint32_t best = uint32_t(kInfI);
             for (uint32_t s = 0; s < nsites; ++s) {
@@ -267,7 +325,10 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
         if (lane == 0) k = atomicAdd(&claim, 1u);
         return __builtin_amdgcn_readfirstlane(k);
     };
-    const uint32_t npatch = uint32_t(n / 16);
+    const uint32_t npatch = uint32_t((n + 15) / 16);
+    // RAG: this lane's two lines adjacent in memory
+    const uint64_t base0 = RAG ? line_base[2 * jw] : base + uint32_t(2 * jw);
+    const bool two = !RAG || (uint32_t(2 * jw + 1) < nlive && line_base[2 * jw + 1] == base0 + 1);
     // Results past 16 bits come in regions (far from any site), so a wave
     // that needed the exact search on a patch starts its next patch there,
     // until a patch's results all fit 16 bits again.
@@ -278,7 +339,7 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
         bool redo = wide;
         if (!wide) {
             u16x2 bA, bB;
-            lp_search(code, n, q, jw, bA, bB);
+            lp_search<RAG>(code, n, q, jw, bA, bB);
             h[0] = bA.x;
             h[1] = bA.y;
             h[2] = bB.x;
@@ -287,7 +348,7 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
         }
         if (__builtin_expect(redo, 0)) {
             // a distance of 256 or more, or no site: the patch on the exact copy
-            lp_search32(exact, n, q, 2 * jw, h);
+            lp_search32<RAG>(exact, n, q, 2 * jw, h);
             wide = __any(h[0] >= 0xfffeu || h[1] >= 0xfffeu || h[2] >= 0xfffeu || h[3] >= 0xfffeu);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -300,17 +361,23 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
         // every result exact in 16 bits: the two lines of each row in one store
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const uint64_t e = base + uint64_t(q + k) * a.inner + uint32_t(2 * jw);
             const uint32_t v0 = h[2 * k], v1 = h[2 * k + 1];
+            if (RAG && (q + k >= n || !two)) {
+                emit(q + k, 2 * jw, v0, false);
+                emit(q + k, 2 * jw + 1, v1, false);
+                continue;
+            }
+            const uint64_t e = base0 + uint64_t(q + k) * a.inner;
             if (!FINAL) {
-                *reinterpret_cast<int2 *>(a.buf + e) = int2{int32_t(v0), int32_t(v1)};
+                *reinterpret_cast<int2u *>(a.buf + e) = int2u{int32_t(v0), int32_t(v1)};
                 continue;
             }
             const bool small = v0 < uint32_t(kLpLut) && v1 < uint32_t(kLpLut);
             const float d0 = small ? __builtin_bit_cast(float, lut[v0]) : sqrt_rn_int(v0);
             const float d1 = small ? __builtin_bit_cast(float, lut[v1]) : sqrt_rn_int(v1);
-            if (a.dist) *reinterpret_cast<float2 *>(a.dist + e) = float2{d0, d1};
-            if (a.sq) *reinterpret_cast<int2 *>(a.sq + e) = int2{int32_t(v0), int32_t(v1)};
+            if (a.dist)
+                *reinterpret_cast<int2u *>(a.dist + e) = int2u{__builtin_bit_cast(int, d0), __builtin_bit_cast(int, d1)};
+            if (a.sq) *reinterpret_cast<int2u *>(a.sq + e) = int2u{int32_t(v0), int32_t(v1)};
         }
     }
 }
