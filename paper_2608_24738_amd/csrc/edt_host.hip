@@ -1073,7 +1073,15 @@ int run(Request &r) {
                 la.wall[b] = r.w[b];
             }
             if (order_n && a == 0 && p.ls_lpw == 8 && lines == 32 * order_n) la.order = r.ws + order_n;
-            const dim3 lgrid(uint32_t((lines + p.ls_lpw - 1) / p.ls_lpw)), lblock(kWave * kLsWaves);
+            // no more waves than rows to search, and with many workgroups a
+            // wave per three steps of rows: short lines left most of 16 waves idle
+            // (signed 27 x 43 x 91 x 34 44 + 58 -> 29 + 25 us, 5 x 208 x 34 x 224
+            // 181 + 75 -> 79 + 65 us; 12 x 153 x 208, 312 workgroups, 7.6 against
+            // 8.5 us with a third of the waves)
+            const uint64_t lgroups = (lines + p.ls_lpw - 1) / p.ls_lpw;
+            const uint32_t lrows = uint32_t(kWave / p.ls_lpw) * (lgroups >= 2048 ? 3 : 1);
+            const dim3 lgrid(uint32_t((lines + p.ls_lpw - 1) / p.ls_lpw)),
+                lblock(kWave * std::min<uint32_t>(kLsWaves, (n + lrows - 1) / lrows));
             const char *nm = r.metric == kL2 ? (fin ? "line_search_final" : "line_search")
                                              : (fin ? "cdt_line_final" : "cdt_line");
 #define TM_LS4(M, F, W, S)                                                                                 \

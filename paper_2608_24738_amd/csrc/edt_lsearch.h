@@ -121,7 +121,8 @@ __global__ void __launch_bounds__(kWave * kLsWaves) k_line_search(LineSearchArgs
     using T = typename std::conditional<W16, uint16_t, uint32_t>::type;
     constexpr uint32_t NONE = W16 ? 0xffffu : 0xffffffffu;
     constexpr int RPW = kWave / LPW;                 // rows per wave and step
-    constexpr int STEP = kLsWaves * RPW;             // row step of one lane
+    const int nthreads = int(blockDim.x), nwaves = nthreads / kWave;
+    const int STEP = nwaves * RPW;                   // row step of one lane
     extern __shared__ __attribute__((aligned(16))) uint8_t ls_lds[];
     __shared__ uint32_t has_site[LPW];       // sites on the line
     __shared__ uint16_t site_row[LPW][kLsDirect];
@@ -159,7 +160,7 @@ __global__ void __launch_bounds__(kWave * kLsWaves) k_line_search(LineSearchArgs
     T *row0 = tile + kLsGuard * LPW;
 
     if (!SIGNED) {
-        for (int k = t; k < kLsGuard * LPW; k += kWave * kLsWaves) {
+        for (int k = t; k < kLsGuard * LPW; k += nthreads) {
             tile[k] = T(NONE);
             row0[n * LPW + k] = T(NONE);
         }
@@ -174,7 +175,8 @@ __global__ void __launch_bounds__(kWave * kLsWaves) k_line_search(LineSearchArgs
     if constexpr (PK) {
         // one packed word per lane and row: lines 2 jp and 2 jp + 1 (the
         // grid covers whole strips: every line is live), 4 lanes per row
-        constexpr int RPW2 = 2 * RPW, STEP2 = kLsWaves * RPW2;
+        constexpr int RPW2 = 2 * RPW;
+        const int STEP2 = nwaves * RPW2;
         const int jp = lane % (LPW / 2), sub2 = lane / (LPW / 2);
         const uint32_t *strip = reinterpret_cast<const uint32_t *>(a.buf + (base - uint32_t(j)));
         uint32_t seen_hi = 0;
@@ -254,21 +256,22 @@ __global__ void __launch_bounds__(kWave * kLsWaves) k_line_search(LineSearchArgs
     bool few = DIRECT;
 #pragma unroll
     for (int k = 0; k < LPW; ++k) few &= has_site[k] <= uint32_t(kLsDirect);
-    if (few && wv < LPW && has_site[wv] != 0u) {
-        const T *colw = row0 + wv;
+    for (int lw = wv; few && lw < LPW; lw += nwaves) {
+        if (has_site[lw] == 0u) continue;
+        const T *colw = row0 + lw;
         uint32_t cnt = 0;
         for (int qb = 0; qb < n; qb += kWave) {
             const int q = qb + lane;
             const bool site = q < n && uint32_t(colw[q * LPW]) < NONE;
             const uint64_t b = __ballot(site);
             const uint32_t pos = cnt + uint32_t(__builtin_popcountll(b & ((uint64_t(1) << lane) - 1)));
-            if (site && pos < uint32_t(kLsDirect)) site_row[wv][pos] = uint16_t(q);
+            if (site && pos < uint32_t(kLsDirect)) site_row[lw][pos] = uint16_t(q);
             cnt += uint32_t(__builtin_popcountll(b));
         }
     }
     if (few) __syncthreads();
     if (SIGNED) {
-        for (int k = t; k < kLsGuard * LPW; k += kWave * kLsWaves) {
+        for (int k = t; k < kLsGuard * LPW; k += nthreads) {
             tile[k] = row0[k % LPW];
             row0[n * LPW + k] = row0[(n - 1) * LPW + k % LPW];
         }
