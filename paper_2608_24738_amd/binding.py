@@ -16,6 +16,8 @@ wrappers (``distance_transform_edt``, ``distance_transform_bf``,
 from __future__ import annotations
 
 import ctypes
+import functools
+import math
 import os
 import threading
 
@@ -38,6 +40,8 @@ class TMError(RuntimeError):
 def load() -> ctypes.CDLL:
     """Open the library (once). Raises if it has not been built."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -89,20 +93,46 @@ def tm_strerror(status: int) -> str:
     return load().tm_strerror(int(status)).decode()
 
 
-def _stream_handle(stream) -> int:
+# Host time per call counts on small inputs (one kernel of 4 us): the device
+# guard is entered only for another device than the current one, the current
+# stream's handle comes without a Stream object, shapes are turned into C arrays
+# once per distinct shape, and pointers go to ctypes as plain integers.
+# 1 x 64^2 with indices: 18.5 -> 10 us per call.
+def _call(name: str, dev: torch.device, stream, *args) -> None:
+    """Calls the C entry `name` with `args` and the stream handle (the current
+    stream of `dev` if None), with `dev` current; raises on an error status."""
+    fn = getattr(load(), name)
+    if torch._C._cuda_getDevice() == dev.index:
+        rc = fn(*args, _stream_handle(stream, dev.index))
+    else:
+        with torch.cuda.device(dev):
+            rc = fn(*args, _stream_handle(stream, dev.index))
+    if rc != TM_OK:
+        raise TMError(rc, name)
+
+
+def _stream_handle(stream, index: int) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(index)
     return int(stream.cuda_stream)
+
+
+@functools.lru_cache(maxsize=1024)
+def _shape_array(shape: tuple):
+    return (ctypes.c_int64 * len(shape))(*shape)
+
+
+def _sampling_array(sampling, ndim):
+    if sampling is None:
+        return None
+    return (ctypes.c_double * ndim)(*[float(s) for s in sampling])
 
 
 def _shape_args(x: torch.Tensor, ndim: int):
     if x.dim() < ndim:
         raise ValueError("input has fewer than ndim=%d dimensions" % ndim)
-    spatial = tuple(int(s) for s in x.shape[x.dim() - ndim:])
-    batch = 1
-    for s in x.shape[:x.dim() - ndim]:
-        batch *= int(s)
-    return spatial, batch
+    lead = x.dim() - ndim
+    return tuple(x.shape[lead:]), math.prod(x.shape[:lead])
 
 
 def _check_mask(in_u8: torch.Tensor):
@@ -116,7 +146,7 @@ def _check_mask(in_u8: torch.Tensor):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check_out(t, dtype, numel, name, dev):
@@ -135,25 +165,14 @@ def tm_edt(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None, out_idx
     vox = in_u8.numel() // max(batch, 1)
     _check_out(out_dist, torch.float32, batch * vox, "out_dist", in_u8.device)
     _check_out(out_idx, torch.int32, batch * vox * ndim, "out_idx", in_u8.device)
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    samp = None
-    if sampling is not None:
-        samp = (ctypes.c_double * ndim)(*[float(s) for s in sampling])
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_edt(_ptr(in_u8), ndim, shape, batch, samp, _ptr(out_dist), _ptr(out_idx),
-                           ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_edt")
+    _call("tm_edt", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch,
+          _sampling_array(sampling, ndim), _ptr(out_dist), _ptr(out_idx))
 
 
 def tm_edt_workspace_size(ndim: int, spatial, batch: int, sampling=None, with_indices=False) -> int:
     """Calls tm_edt_workspace_size: bytes of workspace tm_edt_ws uses (0: none)."""
-    shape = (ctypes.c_int64 * ndim)(*[int(v) for v in spatial])
-    samp = None
-    if sampling is not None:
-        samp = (ctypes.c_double * ndim)(*[float(v) for v in sampling])
-    return int(load().tm_edt_workspace_size(ndim, shape, int(batch), samp, 1 if with_indices else 0))
+    return int(load().tm_edt_workspace_size(ndim, _shape_array(tuple([int(v) for v in spatial])), int(batch),
+                                            _sampling_array(sampling, ndim), 1 if with_indices else 0))
 
 
 def tm_edt_ws(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None, out_idx=None,
@@ -170,16 +189,8 @@ def tm_edt_ws(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None, out_
         if workspace.device != in_u8.device or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous tensor on %s" % in_u8.device)
         nbytes = workspace.numel() * workspace.element_size()
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    samp = None
-    if sampling is not None:
-        samp = (ctypes.c_double * ndim)(*[float(v) for v in sampling])
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_edt_ws(_ptr(in_u8), ndim, shape, batch, samp, _ptr(out_dist), _ptr(out_idx),
-                              _ptr(workspace), nbytes, ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_edt_ws")
+    _call("tm_edt_ws", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch,
+          _sampling_array(sampling, ndim), _ptr(out_dist), _ptr(out_idx), _ptr(workspace), nbytes)
 
 
 def tm_edt_noalloc(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None, out_idx=None,
@@ -190,16 +201,8 @@ def tm_edt_noalloc(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None,
     vox = in_u8.numel() // max(batch, 1)
     _check_out(out_dist, torch.float32, batch * vox, "out_dist", in_u8.device)
     _check_out(out_idx, torch.int32, batch * vox * ndim, "out_idx", in_u8.device)
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    samp = None
-    if sampling is not None:
-        samp = (ctypes.c_double * ndim)(*[float(v) for v in sampling])
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_edt_noalloc(_ptr(in_u8), ndim, shape, batch, samp, _ptr(out_dist), _ptr(out_idx),
-                                   ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_edt_noalloc")
+    _call("tm_edt_noalloc", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch,
+          _sampling_array(sampling, ndim), _ptr(out_dist), _ptr(out_idx))
 
 
 # Workspaces of the scipy-style wrapper, one per (device, stream): calls on one
@@ -210,11 +213,21 @@ _workspaces = {}
 _UNORDERED_ROWS = range(640, 2049)
 
 
+@functools.lru_cache(maxsize=1024)
+def _order_bytes(entry: str, spatial: tuple, batch: int) -> int:
+    """Workspace the wrappers keep for a unit-sampled distance request: only
+    2-D column passes keep an order."""
+    if len(spatial) != 2 or spatial[0] in _UNORDERED_ROWS:
+        return 0
+    if entry == "tm_cdt":
+        return tm_cdt_workspace_size(2, spatial, batch, METRICS["chessboard"])
+    return tm_edt_workspace_size(2, spatial, batch)
+
+
 def _workspace(dev, nbytes: int, stream=None):
     if nbytes <= 0:
         return None
-    with torch.cuda.device(dev):
-        key = (dev.index, _stream_handle(stream))
+    key = (dev.index, _stream_handle(stream, dev.index))
     with _lock:
         ws = _workspaces.get(key)
         if ws is None or ws.numel() * 4 < nbytes:
@@ -230,13 +243,8 @@ def tm_edt_sq(in_u8: torch.Tensor, ndim: int, out_sq=None, out_idx=None, stream=
     vox = in_u8.numel() // max(batch, 1)
     _check_out(out_sq, torch.int32, batch * vox, "out_sq", in_u8.device)
     _check_out(out_idx, torch.int32, batch * vox * ndim, "out_idx", in_u8.device)
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_edt_sq(_ptr(in_u8), ndim, shape, batch, _ptr(out_sq), _ptr(out_idx),
-                              ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_edt_sq")
+    _call("tm_edt_sq", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch, _ptr(out_sq),
+          _ptr(out_idx))
 
 
 METRICS = {"euclidean": 0, "taxicab": 1, "chessboard": 2}
@@ -250,16 +258,8 @@ def tm_dt_bf(in_u8: torch.Tensor, ndim: int, metric: int, sampling=None, out_dis
     vox = in_u8.numel() // max(batch, 1)
     _check_out(out_dist, torch.float32, batch * vox, "out_dist", in_u8.device)
     _check_out(out_idx, torch.int32, batch * vox * ndim, "out_idx", in_u8.device)
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    samp = None
-    if sampling is not None:
-        samp = (ctypes.c_double * ndim)(*[float(s) for s in sampling])
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_dt_bf(_ptr(in_u8), ndim, shape, batch, int(metric), samp, _ptr(out_dist),
-                             _ptr(out_idx), ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_dt_bf")
+    _call("tm_dt_bf", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch, int(metric),
+          _sampling_array(sampling, ndim), _ptr(out_dist), _ptr(out_idx))
 
 
 def tm_edt_signed(in_u8: torch.Tensor, ndim: int, out_dist, stream=None) -> None:
@@ -268,12 +268,7 @@ def tm_edt_signed(in_u8: torch.Tensor, ndim: int, out_dist, stream=None) -> None
     spatial, batch = _shape_args(in_u8, ndim)
     vox = in_u8.numel() // max(batch, 1)
     _check_out(out_dist, torch.float32, batch * vox, "out_dist", in_u8.device)
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_edt_signed(_ptr(in_u8), ndim, shape, batch, _ptr(out_dist), ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_edt_signed")
+    _call("tm_edt_signed", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch, _ptr(out_dist))
 
 
 def tm_cdt(in_u8: torch.Tensor, ndim: int, metric: int, out_dist, stream=None) -> None:
@@ -282,19 +277,14 @@ def tm_cdt(in_u8: torch.Tensor, ndim: int, metric: int, out_dist, stream=None) -
     spatial, batch = _shape_args(in_u8, ndim)
     vox = in_u8.numel() // max(batch, 1)
     _check_out(out_dist, torch.int32, batch * vox, "out_dist", in_u8.device)
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_cdt(_ptr(in_u8), ndim, shape, batch, int(metric), _ptr(out_dist),
-                           ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_cdt")
+    _call("tm_cdt", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch, int(metric),
+          _ptr(out_dist))
 
 
 def tm_cdt_workspace_size(ndim: int, spatial, batch: int, metric: int) -> int:
     """Calls tm_cdt_workspace_size: bytes of workspace tm_cdt_ws uses (0: none)."""
-    shape = (ctypes.c_int64 * ndim)(*[int(v) for v in spatial])
-    return int(load().tm_cdt_workspace_size(ndim, shape, int(batch), int(metric)))
+    return int(load().tm_cdt_workspace_size(ndim, _shape_array(tuple([int(v) for v in spatial])), int(batch),
+                                            int(metric)))
 
 
 def tm_cdt_ws(in_u8: torch.Tensor, ndim: int, metric: int, out_dist, workspace=None, stream=None) -> None:
@@ -309,13 +299,8 @@ def tm_cdt_ws(in_u8: torch.Tensor, ndim: int, metric: int, out_dist, workspace=N
         if workspace.device != in_u8.device or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous tensor on %s" % in_u8.device)
         nbytes = workspace.numel() * workspace.element_size()
-    shape = (ctypes.c_int64 * ndim)(*spatial)
-    with torch.cuda.device(in_u8.device):
-        st = _stream_handle(stream)
-        rc = load().tm_cdt_ws(_ptr(in_u8), ndim, shape, batch, int(metric), _ptr(out_dist), _ptr(workspace),
-                              nbytes, ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_cdt_ws")
+    _call("tm_cdt_ws", in_u8.device, stream, _ptr(in_u8), ndim, _shape_array(spatial), batch, int(metric),
+          _ptr(out_dist), _ptr(workspace), nbytes)
 
 
 def _normalise_sampling(sampling, ndim):
@@ -355,14 +340,10 @@ def tm_mask_nonzero(x: torch.Tensor, out_u8: torch.Tensor, stream=None) -> None:
         raise TypeError("input dtype %s has no nonzero test here" % x.dtype)
     _check_out(out_u8, torch.uint8, x.numel(), "out_u8", x.device)
     nd = max(x.dim(), 1)
-    shape = (ctypes.c_int64 * nd)(*(x.shape if x.dim() else (1,)))
-    strides = (ctypes.c_int64 * nd)(*[st * x.element_size() for st in (x.stride() if x.dim() else (1,))])
-    with torch.cuda.device(x.device):
-        st = _stream_handle(stream)
-        rc = load().tm_mask_nonzero(_ptr(x), _DTYPES[x.dtype], nd, shape, strides, _ptr(out_u8),
-                                    ctypes.c_void_p(st))
-    if rc != TM_OK:
-        raise TMError(rc, "tm_mask_nonzero")
+    size = x.element_size()
+    strides = tuple([st * size for st in x.stride()]) if x.dim() else (size,)
+    _call("tm_mask_nonzero", x.device, stream, _ptr(x), _DTYPES[x.dtype], nd,
+          _shape_array(tuple(x.shape) if x.dim() else (1,)), _shape_array(strides), _ptr(out_u8))
 
 
 def _as_mask(input: torch.Tensor) -> torch.Tensor:
@@ -373,7 +354,7 @@ def _as_mask(input: torch.Tensor) -> torch.Tensor:
     if not input.is_cuda:
         raise ValueError("input must be a ROCm (cuda) tensor")
     if input.dtype in (torch.uint8, torch.bool) and input.is_contiguous():
-        return input.view(torch.uint8)
+        return input
     mask = torch.empty(input.shape, dtype=torch.uint8, device=input.device)
     tm_mask_nonzero(input, mask)
     return mask
@@ -424,11 +405,12 @@ def distance_transform_edt(input: torch.Tensor, sampling=None, return_distances:
         dist_out, dist_back = _out_buffer(distances, mask.shape, torch.float32, dev, "distances")
     if return_indices:
         idx_out, idx_back = _out_buffer(indices, lead + (ndim,) + spatial, torch.int32, dev, "indices")
-    batch = int(lead[0]) * int(lead[1])
+    batch = lead[0] * lead[1]
     ws = None
-    if spatial[0] not in _UNORDERED_ROWS:
-        ws = _workspace(dev, tm_edt_workspace_size(ndim, spatial, batch, samp, return_indices))
-    tm_edt_ws(mask, ndim, samp, dist_out, idx_out, ws)
+    if not return_indices and (samp is None or all(v == 1.0 for v in samp)):
+        ws = _workspace(dev, _order_bytes("tm_edt", spatial, batch))
+    _call("tm_edt_ws", dev, None, mask.data_ptr(), ndim, _shape_array(spatial), batch, _sampling_array(samp, ndim),
+          _ptr(dist_out), _ptr(idx_out), _ptr(ws), 0 if ws is None else ws.numel() * 4)
     if dist_back is not None:
         dist_back.copy_(dist_out)
     if idx_back is not None:
@@ -482,11 +464,13 @@ def distance_transform_cdt(input: torch.Tensor, metric: str = "chessboard", dist
         raise ValueError("metric must be 'chessboard' or 'taxicab'")
     mask = _as_mask(input)
     out, back = _out_buffer(distances, mask.shape, torch.int32, mask.device, "distances")
-    batch = int(mask.shape[0]) * int(mask.shape[1])
+    shape = tuple(mask.shape)
+    batch = shape[0] * shape[1]
     ws = None
-    if mask.shape[2] not in _UNORDERED_ROWS:
-        ws = _workspace(mask.device, tm_cdt_workspace_size(ndim, tuple(mask.shape[2:]), batch, METRICS[metric]))
-    tm_cdt_ws(mask, ndim, METRICS[metric], out, ws)
+    if metric == "chessboard":
+        ws = _workspace(mask.device, _order_bytes("tm_cdt", shape[2:], batch))
+    _call("tm_cdt_ws", mask.device, None, mask.data_ptr(), ndim, _shape_array(shape[2:]), batch, METRICS[metric],
+          out.data_ptr(), _ptr(ws), 0 if ws is None else ws.numel() * 4)
     if back is not None:
         back.copy_(out)
     return None if distances is not None else out
@@ -502,7 +486,9 @@ def signed_distance_transform(input: torch.Tensor, distances=None):
     ndim = input.dim() - 2
     mask = _as_mask(input)
     out, back = _out_buffer(distances, mask.shape, torch.float32, mask.device, "distances")
-    tm_edt_signed(mask, ndim, out)
+    shape = tuple(mask.shape)
+    _call("tm_edt_signed", mask.device, None, mask.data_ptr(), ndim, _shape_array(shape[2:]), shape[0] * shape[1],
+          out.data_ptr())
     if back is not None:
         back.copy_(out)
     return None if distances is not None else out
