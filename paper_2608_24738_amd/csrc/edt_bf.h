@@ -11,6 +11,16 @@
 // so ties go to the smallest flat index.  The coordinate loop is unrolled
 // for ranks 2 and 3 (other ranks loop over the rank).  Unit sampling is
 // exact integer arithmetic; sampled values are float.
+//
+// Two things bounded it on sparse masks (8 x 256^2, 1 % background: 163 us): 64
+// chunks of 1024 bytes per workgroup, each with ten background elements and three
+// barriers, and 32-bit multiplies (a quarter of the rate of 24-bit ones).
+// Chunks are now 4096 bytes for ranks 2 and 3, and unit euclidean transforms
+// whose squared extents sum to at most 2^21 (KEY) take
+//     d^2 - |x|^2 = |y|^2 - 2 x . y
+// with the list's number below it in one 32-bit key: one 24-bit multiply-add per
+// axis and half a minimum per pair of elements.  63 us (8 x 256^2; chunks of 2048
+// bytes 87 us, two elements per thread 83 us).
 #pragma once
 
 #include "edt_common.h"
@@ -20,7 +30,11 @@ namespace tmedt {
 constexpr int kBfThreads = 256;
 constexpr int kBfPer = 4;                        // elements per thread
 constexpr int kBfOut = kBfThreads * kBfPer;      // elements per workgroup
-constexpr int kBfChunk = kBfThreads * 4;         // mask bytes per chunk
+// mask bytes per thread and chunk (and so list entries per chunk), by rank
+__host__ __device__ constexpr int bf_bytes(int nd) { return nd > 0 ? 16 : 4; }
+constexpr int kBfKeyBits = 10;                   // KEY: bits of the number in a key
+constexpr int kBfRun = 1 << kBfKeyBits;          // KEY: list entries between two merges
+constexpr uint64_t kBfKeySum = uint64_t(1) << (31 - kBfKeyBits);   // KEY: most the squared extents sum to
 
 struct BfArgs {
     const uint8_t *in;      // [batch][vox]
@@ -34,12 +48,16 @@ struct BfArgs {
     double sd[kMaxDim];     // the same in double (virtual element)
 };
 
-template <int METRIC, bool SAMP, int ND>
+template <int METRIC, bool SAMP, int ND, bool KEY = false>
 __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
     using V = typename std::conditional<SAMP, float, int32_t>::type;
     constexpr int MAXND = ND > 0 ? ND : kMaxDim;
-    __shared__ V zc[kBfChunk][MAXND];          // background coordinates of the chunk
-    __shared__ uint32_t zflat[kBfChunk];       // their flat indices
+    static_assert(!KEY || (METRIC == 0 && !SAMP && ND > 0), "keys: exact euclidean, rank 2 or 3");
+    constexpr int PB = bf_bytes(ND), kBfChunk = kBfThreads * PB;
+    __shared__ V zc[KEY ? 1 : kBfChunk][MAXND];   // background coordinates of the chunk
+    // KEY: coordinates << kBfKeyBits and (sum of their squares << kBfKeyBits | number)
+    __shared__ int4 zk[KEY ? kBfChunk + 4 : 1];
+    __shared__ uint32_t zflat[KEY ? 1 : kBfChunk];   // their flat indices
     __shared__ uint32_t wave_tot[kBfThreads / kWave];
     const int nd = ND > 0 ? ND : a.ndim;
     const int t = threadIdx.x;
@@ -64,6 +82,7 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
     V x[kBfPer][MAXND];
     V best[kBfPer];
     uint32_t arg[kBfPer];
+    int32_t xx[kBfPer];                     // KEY: squared length of the coordinates
 #pragma unroll
     for (int j = 0; j < kBfPer; ++j) {
         e[j] = blk * uint32_t(kBfOut) + uint32_t(j * kBfThreads + t);
@@ -71,28 +90,56 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
         decode(min(e[j], a.vox - 1), c);
 #pragma unroll
         for (int k = 0; k < MAXND; ++k)
-            if (k < nd) x[j][k] = SAMP ? V(float(c[k]) * a.s[k]) : V(c[k]);
+            if (k < nd) x[j][k] = KEY ? V(-2 * c[k]) : SAMP ? V(float(c[k]) * a.s[k]) : V(c[k]);
+        xx[j] = 0;
+        if constexpr (KEY) {
+#pragma unroll
+            for (int k = 0; k < MAXND; ++k) xx[j] += c[k] * c[k];
+        }
         if constexpr (SAMP) best[j] = __builtin_inff();
         else best[j] = 0x7fffffff;
         arg[j] = 0xffffffffu;
     }
 
-    for (uint32_t c0 = 0; c0 < a.vox; c0 += kBfChunk) {
-        // ---- compact the chunk's background elements, in row-major order ----
-        const uint32_t p0 = c0 + uint32_t(t) * 4;
+    // PB mask bytes from p (foreground past the end), and their zeros
+    struct Bytes {
+        uint32_t w[PB / 4];
+    };
+    auto fetch = [&](Bytes &y, uint32_t p) {
+        if (PB == 16 && p + PB <= a.vox && (uintptr_t(m) + p) % 16 == 0) {
+            const uint4 w = *reinterpret_cast<const uint4 *>(m + p);
+            const uint32_t d4[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < PB / 4; ++j) y.w[j] = d4[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < PB / 4; ++j) y.w[j] = 0;
+#pragma unroll
+            for (int j = 0; j < PB; ++j) y.w[j / 4] |= uint32_t(m[min(p + j, a.vox - 1)]) << (8 * (j % 4));
+        }
+    };
+    auto zero_flags = [&](const Bytes &y, uint32_t p) {
         uint32_t flags = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (p0 + j < a.vox && m[p0 + j] == 0) flags |= 1u << j;
-        uint32_t before = 0, total = 0;
+        for (int j = 0; j < PB; ++j)
+            if (p + j < a.vox && ((y.w[j / 4] >> (8 * (j % 4))) & 0xffu) == 0) flags |= 1u << j;
+        return flags;
+    };
+    Bytes cur;
+    fetch(cur, uint32_t(t) * PB);
+    for (uint32_t c0 = 0; c0 < a.vox; c0 += kBfChunk) {
+        // ---- compact the chunk's background elements, in row-major order ----
+        const uint32_t p0 = c0 + uint32_t(t) * PB;
+        uint32_t flags = zero_flags(cur, p0);
+        // the next chunk's bytes, on their way while this one's list runs
+        if (c0 + kBfChunk < a.vox) fetch(cur, p0 + kBfChunk);
+        uint32_t upto = __popc(flags);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint64_t bal = __ballot((flags >> j) & 1u);
-            const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-            before += __popcll(bal & lt);
-            total += __popcll(bal);
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t u = __shfl_up(upto, d, kWave);
+            upto += lane >= d ? u : 0u;
         }
-        if (lane == 0) wave_tot[wv] = total;
+        if (lane == kWave - 1) wave_tot[wv] = upto;
         __syncthreads();
         uint32_t base = 0, count = 0;
 #pragma unroll
@@ -100,20 +147,64 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
             if (w < wv) base += wave_tot[w];
             count += wave_tot[w];
         }
-        uint32_t pos = base + before;
+        uint32_t pos = base + upto - __popc(flags);
+        for (; flags; flags &= flags - 1) {
+            const uint32_t f = p0 + uint32_t(__ffs(flags) - 1);
+            int32_t c[MAXND];
+            decode(f, c);
+            if constexpr (KEY) {
+                int32_t yy = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if ((flags >> j) & 1u) {
-                int32_t c[MAXND];
-                decode(p0 + j, c);
+                for (int k = 0; k < MAXND; ++k) yy += c[k] * c[k];
+                zk[pos] = make_int4(c[0] << kBfKeyBits, c[1] << kBfKeyBits, MAXND > 2 ? c[MAXND - 1] << kBfKeyBits : 0,
+                                    (yy << kBfKeyBits) | int32_t(pos % kBfRun));
+            } else {
 #pragma unroll
                 for (int k = 0; k < MAXND; ++k)
                     if (k < nd) zc[pos][k] = SAMP ? V(float(c[k]) * a.s[k]) : V(c[k]);
-                zflat[pos] = p0 + j;
-                ++pos;
             }
+            if (!KEY) zflat[pos] = f;
+            ++pos;
         }
+        if (KEY && t < 4) zk[count + t] = make_int4(0, 0, 0, 0x7fffffff);   // whole fours
         __syncthreads();
+        if constexpr (KEY) {
+            for (uint32_t z0 = 0; z0 < count; z0 += kBfRun) {
+                const uint32_t z1 = min(count, z0 + kBfRun);
+                int32_t key[kBfPer];
+#pragma unroll
+                for (int j = 0; j < kBfPer; ++j) key[j] = 0x7fffffff;
+                for (uint32_t z = z0; z < z1; z += 4) {
+                    int4 y[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) y[i] = zk[z + i];
+#pragma unroll
+                    for (int j = 0; j < kBfPer; ++j) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            // (sums wrap modulo 2^32; the key itself fits)
+                            int32_t v = __mul24(x[j][0], y[i].x) + y[i].w;
+                            v = __mul24(x[j][1], y[i].y) + v;
+                            if (MAXND > 2) v = __mul24(x[j][MAXND - 1], y[i].z) + v;
+                            key[j] = min(key[j], v);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kBfPer; ++j) {
+                    const int32_t v = (key[j] >> kBfKeyBits) + xx[j];
+                    if (v < best[j]) {
+                        best[j] = v;
+                        const int4 y = zk[z0 + uint32_t(key[j] & (kBfRun - 1))];
+                        uint32_t f = uint32_t(y.x >> kBfKeyBits) * a.div_shape[1].d + uint32_t(y.y >> kBfKeyBits);
+                        if (MAXND > 2) f = f * a.div_shape[MAXND - 1].d + uint32_t(y.z >> kBfKeyBits);
+                        arg[j] = 0x80000000u | f;
+                    }
+                }
+            }
+            __syncthreads();
+            continue;
+        }
         // ---- run the list against this thread's elements ----------------------
         for (uint32_t z = 0; z < count; ++z) {
             V y[MAXND];

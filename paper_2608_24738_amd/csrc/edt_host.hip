@@ -1403,7 +1403,13 @@ extern "C" int tm_dt_bf(const uint8_t *in_u8, int ndim, const int64_t *shape, in
     (ndim == 2   ? launch("dt_bf", k_dt_bf<M, S, 2>, grid, block, 0, stream, x)                   \
      : ndim == 3 ? launch("dt_bf", k_dt_bf<M, S, 3>, grid, block, 0, stream, x)                   \
                  : launch("dt_bf", k_dt_bf<M, S, 0>, grid, block, 0, stream, x))
-    if (metric == TM_METRIC_EUCLIDEAN) rc = samp ? TM_BF(0, true) : TM_BF(0, false);
+    // exact euclidean: value and number in one key while the squared extents allow
+    uint64_t sumsq = 0;
+    for (int a = 0; a < ndim; ++a) sumsq += uint64_t(r.shape[a]) * r.shape[a];
+    if (metric == TM_METRIC_EUCLIDEAN && !samp && (ndim == 2 || ndim == 3) && sumsq <= kBfKeySum)
+        rc = ndim == 2 ? launch("dt_bf", k_dt_bf<0, false, 2, true>, grid, block, 0, stream, x)
+                       : launch("dt_bf", k_dt_bf<0, false, 3, true>, grid, block, 0, stream, x);
+    else if (metric == TM_METRIC_EUCLIDEAN) rc = samp ? TM_BF(0, true) : TM_BF(0, false);
     else if (metric == TM_METRIC_TAXICAB) rc = samp ? TM_BF(1, true) : TM_BF(1, false);
     else rc = samp ? TM_BF(2, true) : TM_BF(2, false);
 #undef TM_BF
