@@ -135,21 +135,24 @@ __device__ inline void scan_store(const ScanArgs &a, uint32_t gline, int x, int 
 }
 
 // Lines of length n <= 1024: each wavefront scans `span_lines` whole lines, at
-// most 1024 positions, lane l holding positions 64 k + l.  A chunk's zeros are
-// one ballot; the distance to the nearest zero on each side comes from the
-// ballot's bits up to and from the lane, or from the last zero before and the
-// first one after the chunk (the same for all lanes), and counts when it stays in
-// the lane's line.
-// Loads read 64 and stores write 256 contiguous bytes whatever the line length.
+// most 1024 positions, in chunks of 256 of which lane l holds the four
+// consecutive ones 256 k + 4 l ... (unaligned 4-byte loads, 16-byte stores aligned
+// to 4: contiguous whatever the line length).  The last zero before a lane's four
+// positions lies in the nearest lower lane that has one (a ballot's bits give it,
+// a lane permute its position) or before the chunk, the first one after them
+// likewise; the lane then walks its four positions both ways, forgetting zeros
+// at line starts.
 //
-// Bound by VALU issue (about 45 instructions per position):
-// 2 x 155 x 240 x 237 in 34 us, against 41 us with 16 positions per lane in
-// runs of four (per-byte loads and stores 16 bytes apart on odd lengths);
-// 3 x 64 x 213 in 4.1 us, against 7.4 us.
-constexpr int kSpanChunks = kSpan / kWave;
+// Bound by VALU issue (about 28 instructions per position):
+// 2 x 155 x 240 x 237 in 20 us (34 us with one position per lane, 45 instructions
+// each), 16 x 601 x 803 in 14 us, 3 x 64 x 213 in 4.2 us.
+constexpr int kSpanChunk = 4 * kWave;
+constexpr int kSpanChunks = kSpan / kSpanChunk;
 
 template <int MODE>
 __global__ void __launch_bounds__(256) k_scan_span(ScanArgs a) {
+    typedef uint32_t word_u __attribute__((aligned(1)));
+    typedef int int4_u __attribute__((ext_vector_type(4), aligned(4)));
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     const uint64_t line0 = uint64_t(wave) * a.span_lines;
@@ -158,24 +161,36 @@ __global__ void __launch_bounds__(256) k_scan_span(ScanArgs a) {
     const int valid = int(__builtin_amdgcn_readfirstlane(nl * a.n));
     const uint8_t *src = a.in + line0 * a.n;
 
-    uint8_t v[kSpanChunks];
+    // 0x80 in every zero byte of the lane's four positions, none past the end
+    uint32_t zb[kSpanChunks];
 #pragma unroll
     for (int k = 0; k < kSpanChunks; ++k) {
-        if (64 * k >= valid) break;
-        v[k] = src[min(64 * k + lane, valid - 1)];
+        zb[k] = 0;
+        const int p = kSpanChunk * k + 4 * lane;
+        uint32_t w = 0xffffffffu;
+        if (p + 4 <= valid) {
+            w = *reinterpret_cast<const word_u *>(src + p);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (p + j < valid) w = (w & ~(0xffu << (8 * j))) | (uint32_t(src[p + j]) << (8 * j));
+        }
+        zb[k] = ~(((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w | 0x7f7f7f7fu);
     }
-    // zeros of each chunk, and the first zero after it
-    uint64_t zb[kSpanChunks];
+    // lanes with a zero, per chunk, and the first zero after each chunk
+    uint64_t has[kSpanChunks];
     int next[kSpanChunks];
 #pragma unroll
-    for (int k = 0; k < kSpanChunks; ++k) zb[k] = 64 * k < valid ? __ballot(64 * k + lane < valid && v[k] == 0) : 0;
+    for (int k = 0; k < kSpanChunks; ++k) has[k] = __ballot(zb[k] != 0);
+    auto first_in = [&](int k) { return kSpanChunk * k + 4 * lane + (__builtin_ctz(zb[k] | 0x80000000u) >> 3); };
+    auto last_in = [&](int k) { return kSpanChunk * k + 4 * lane + 3 - (__builtin_clz(zb[k] | 1u) >> 3); };
     int nz = kBig;
 #pragma unroll
     for (int k = kSpanChunks - 1; k >= 0; --k) {
         next[k] = nz;
-        if (zb[k]) nz = 64 * k + __builtin_ctzll(zb[k]);
+        if (has[k]) nz = __builtin_amdgcn_readlane(first_in(k), __builtin_ctzll(has[k]));
     }
-    // index carrier: the wave's lines lie in one sample (else per lane)
+    // index carrier: the wave's lines lie in one sample (else per element)
     uint32_t smp = 0, local = 0;
     bool split = false;
     if constexpr (MODE == kScanIndex) {
@@ -184,42 +199,73 @@ __global__ void __launch_bounds__(256) k_scan_span(ScanArgs a) {
         split = local + nl > a.lps;
         local *= a.n;
     }
-    constexpr uint32_t kFar = 1u << 16;                         // no zero in the line
-    const uint32_t rem = uint32_t(kWave) % a.n;
-    uint32_t x = uint32_t(lane) % a.n;                          // position in the line
+    const uint32_t rem = uint32_t(kSpanChunk) % a.n;
+    uint32_t x0 = uint32_t(4 * lane) % a.n;                     // line position of the lane's first element
     int last = -kBig;                                           // last zero before the chunk
 #pragma unroll
     for (int k = 0; k < kSpanChunks; ++k) {
-        if (64 * k >= valid) break;
-        const int p = 64 * k + lane;
-        // distances to the last zero at or before p and to the first one from p
-        // (all ones from an empty half word survives the "or" with 32)
-        const uint64_t lo = zb[k] << (kWave - 1 - lane), hi = zb[k] >> lane;
-        const uint32_t lh = uint32_t(lo >> 32), ll = uint32_t(lo), hh = uint32_t(hi >> 32), hl = uint32_t(hi);
-        auto clz = [](uint32_t w) { return w ? uint32_t(__builtin_clz(w)) : ~0u; };
-        auto ctz = [](uint32_t w) { return w ? uint32_t(__builtin_ctz(w)) : ~0u; };
-        uint32_t dl = min(clz(lh), clz(ll) | 32u);
-        uint32_t dr = min(ctz(hl), ctz(hh) | 32u);
-        dl = min(dl, uint32_t(p - last));
-        dr = min(dr, uint32_t(next[k] - p));
-        if (zb[k]) last = 64 * k + 63 - __builtin_clzll(zb[k]);
-        dl = dl <= x ? dl : kFar;
-        dr = dr < a.n - x ? dr : kFar;
-        const uint32_t d = min(dl, dr);
-        if (p < valid) {
-            if constexpr (MODE == kScanFieldInt || MODE == kScanFieldL1) {
-                a.field_i[line0 * a.n + uint32_t(p)] =
-                    d >= kFar ? kInfI : MODE == kScanFieldL1 ? int32_t(d) : int32_t(__umul24(d, d));
-            } else if (MODE == kScanIndex && !split) {
-                a.idx[uint64_t(smp) * a.cstride + local + uint32_t(p)] =
-                    d >= kFar ? kNoIdx : int32_t(local) + (dl <= dr ? p - int(dl) : p + int(dr));
-            } else {
-                scan_store<MODE>(a, uint32_t(line0) + a.div_n.div(uint32_t(p)), int(x),
-                                 d >= kFar ? -1 : dl <= dr ? int(x - dl) : int(x + dr));
+        if (kSpanChunk * k >= valid) break;
+        const int p = kSpanChunk * k + 4 * lane;
+        const uint64_t lo = (has[k] << (kWave - 1 - lane)) << 1, hi = (has[k] >> lane) >> 1;
+        const int lp = last_in(k), fp = first_in(k);
+        int L = __builtin_amdgcn_ds_bpermute(4 * (lane - 1 - __clzll(lo | 1ull)), lp);
+        int R = __builtin_amdgcn_ds_bpermute(4 * (lane + __ffsll((unsigned long long)hi)), fp);
+        L = lo ? L : last;
+        R = hi ? R : next[k];
+        if (has[k]) last = __builtin_amdgcn_readlane(lp, 63 - __builtin_clzll(has[k]));
+        uint32_t x[4];
+        x[0] = x0;
+#pragma unroll
+        for (int j = 1; j < 4; ++j) x[j] = min(x[j - 1] + 1u, x[j - 1] + 1u - a.n);   // (unsigned: wraps at the line's end)
+        L = uint32_t(p - L) <= x[0] ? L : -kBig;
+        R = uint32_t(R - p - 3) < a.n - x[3] ? R : kBig;
+        int dl[4], dr[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j > 0) L = x[j] == 0 ? -kBig : L;
+            L = (zb[k] >> (8 * j + 7)) & 1u ? p + j : L;
+            dl[j] = p + j - L;
+        }
+#pragma unroll
+        for (int j = 3; j >= 0; --j) {
+            R = (zb[k] >> (8 * j + 7)) & 1u ? p + j : R;
+            dr[j] = R - (p + j);
+            if (j > 0) R = x[j] == 0 ? kBig : R;
+        }
+        constexpr int kFar = kBig / 2;
+        int out[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int d = min(dl[j], dr[j]);
+            if (MODE == kScanFieldInt) out[j] = d >= kFar ? kInfI : __mul24(d, d);
+            else if (MODE == kScanFieldL1) out[j] = d >= kFar ? kInfI : d;
+            else out[j] = d >= kFar ? -1 : dl[j] <= dr[j] ? p + j - dl[j] : p + j + dr[j];   // span position
+        }
+        if constexpr (MODE == kScanFieldInt || MODE == kScanFieldL1 || MODE == kScanIndex) {
+            int32_t *o = MODE == kScanIndex ? a.idx + uint64_t(smp) * a.cstride + local + uint32_t(p)
+                                            : a.field_i + line0 * a.n + uint32_t(p);
+            if (!split) {
+                if (MODE == kScanIndex)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) out[j] = out[j] < 0 ? kNoIdx : out[j] + int(local);
+                if (p + 4 <= valid) {
+                    *reinterpret_cast<int4_u *>(o) = int4_u{out[0], out[1], out[2], out[3]};
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        if (p + j < valid) o[j] = out[j];
+                }
             }
         }
-        x += rem;
-        x = min(x, x - a.n);                                    // (unsigned: less the line length if past it)
+        if (MODE == kScanFieldFlt || MODE == kScanFinal || split) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (p + j < valid)
+                    scan_store<MODE>(a, uint32_t(line0) + a.div_n.div(uint32_t(p + j)), int(x[j]),
+                                     out[j] < 0 ? -1 : out[j] - (p + j - int(x[j])));
+        }
+        x0 += rem;
+        x0 = min(x0, x0 - a.n);
     }
 }
 
