@@ -212,15 +212,24 @@ constexpr uint64_t kPairMinLines = 256 * kPairLines;
 constexpr uint64_t kLpMinGroups = 256;
 constexpr uint64_t kLpMinGroupsRag = 512;
 
-// Rows from which a distance pass takes the bracketed search instead of the
-// whole-line windowed one, whose work grows with the distances.  Measured
-// (column pass, us, windowed -> bracketed): 8 x 1024^2 discs 105 -> 54, balls
-// 137 -> 67, 1 % background 30 -> 30; chessboard 90 -> 49, 124 -> 51, 22 -> 27;
-// 8 x 600 x 803 discs 63 -> 45, balls 48 -> 53, 1 % background 25 -> 23;
-// 16 x 375 x 500 discs 32 -> 36, balls 28 -> 40: shorter lines stay.  Index
-// passes take it where the tiled search ends (256 rows): the envelope with one
-// lane per line takes 516 us on 16 x 375 x 500 balls, the brackets 41 us.
-constexpr uint32_t kBkMinRows = 640;
+// Distance passes take the bracketed search instead of the whole-line windowed
+// one, whose work grows with the distances, where lines and rows are long enough
+// for far distances and groups of 16 lines are many (a workgroup's phases are a
+// chain).  Measured (column pass, us, windowed -> bracketed; balls, discs, 1 %
+// background):
+//   8 x 1024^2          137 -> 67, 105 -> 54, 30 -> 30
+//   8 x 700 x 1024      65 -> 58, 103 -> 44, 21 -> 25 (packed rows: from 896)
+//   8 x 650 x 803       57 -> 54, 72 -> 48, 27 -> 24 (int32 rows: from 640)
+//   6 x 900 x 1024      103 -> 64, 88 -> 51, 21 -> 30 (384 groups)
+//   16 x 650 x 401      36 -> 50, 47 -> 46, 26 -> 29 (401 wide)
+//   4 x 720 x 500       22 -> 42, 30 -> 32, 13 -> 24 (125 groups)
+// Rows of a multiple of 64 are packed to 16 bits for the windowed search, which
+// moves their lines up.  Index passes take the brackets where the tiled search
+// ends (256 rows): the envelope with one lane per line takes 516 us on
+// 16 x 375 x 500 balls, the brackets 40 us.
+constexpr uint32_t kBkMinRows = 640, kBkMinRowsPacked = 896;
+constexpr uint64_t kBkMinGroups = 400, kBkMinGroupsPacked = 512;
+constexpr uint32_t kBkMinWidth = 512;
 
 // Plan of one strided pass.
 struct FhPlan {
@@ -266,7 +275,11 @@ bool plan_line_search(FhPlan &p, uint32_t n, uint64_t total, bool w16, int min_l
 // row scan's distance, or (index) the carrier of a 2-D request.
 bool plan_bracket(FhPlan &p, const Request &r, int a, uint64_t total, bool index_path) {
     const uint32_t n = r.shape[a], w = r.shape[r.ndim - 1];
-    if (!index_path && n < kBkMinRows) return false;
+    const uint64_t groups = (total / n + kBkLines - 1) / kBkLines;
+    const bool packed = w % kWave == 0;
+    if (!index_path && (w < kBkMinWidth || n < (packed ? kBkMinRowsPacked : kBkMinRows) ||
+                        groups < (packed ? kBkMinGroupsPacked : kBkMinGroups)))
+        return false;
     if (a != r.ndim - 2 || !r.unit || r.sgn || w > kBkMaxD || n > kBkMaxN || total / n + kBkLines >= (uint64_t(1) << 32))
         return false;
     if (index_path) {

@@ -39,9 +39,24 @@ def names_of(fn):
         binding.prof_enable(0)
 
 
-# rows at the rule's edge (640), one segment short and over, the last line a
-# 17th or 33rd of its group, the longest line; packed (wide multiples of 64) and not
-SHAPES = [(640, 17), (647, 33), (649, 128), (1024, 256), (2048, 31), (3, 645, 40)]
+# rows at the rule's edges (640, and 896 for rows of a multiple of 64, which go over
+# packed), one segment short and over, partial last groups, the longest line
+SHAPES = [(640, 513), (647, 515), (897, 576), (1024, 512), (2048, 517), (3, 645, 521)]
+
+
+def chessboard(mask):
+    """(B, *spatial) chessboard distances, axis by axis, by shifts on the GPU."""
+    import torch
+    f = torch.where(torch.from_numpy(mask).cuda() == 0, 0, 1 << 20).to(torch.int32)
+    for axis in range(1, f.dim()):
+        best, n = f.clone(), f.shape[axis]
+        for k in range(1, n):
+            lo, hi = f.narrow(axis, 0, n - k), f.narrow(axis, k, n - k)
+            to_lo, to_hi = best.narrow(axis, 0, n - k), best.narrow(axis, k, n - k)
+            torch.minimum(to_hi, lo.clamp(min=k), out=to_hi)
+            torch.minimum(to_lo, hi.clamp(min=k), out=to_lo)
+        f = best
+    return torch.where(f < (1 << 20), f, -1).cpu().numpy()
 
 
 @pytest.mark.parametrize("spatial", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
@@ -50,16 +65,22 @@ def test_distances(spatial):
 
     from paper_2608_24738_amd import binding
     nd = len(spatial)
-    mask = masks(spatial, sum(spatial))
+    once = masks(spatial, sum(spatial))
+    # the rule also asks for 512 groups of 16 lines: the masks several times over
+    reps = -(-512 * 16 * spatial[-2] // once.size) + 1
+    mask = np.tile(once, (reps,) + (1,) * nd)
     announce("bracket distances shape=%s" % (mask.shape,))
     res, names = names_of(lambda: run_gpu(mask, nd, None, dist=True, idx=False, sq=True))
     assert any(n.startswith("line_search") for n in names), names
-    check_against_oracle(mask, nd, None, res, edt_oracle.edt(mask, nd, None, nthreads=16))
+    ora = edt_oracle.edt(once, nd, None, nthreads=16)
+    ora = {k: np.tile(ora[k], (reps,) + (1,) * nd) for k in ("dist", "sq")}
+    check_against_oracle(mask, nd, None, res, ora)
     x = torch.from_numpy(mask).cuda()
     out = torch.empty(mask.shape, dtype=torch.int32, device=x.device)
     _, names = names_of(lambda: (binding.tm_cdt(x, nd, 2, out), torch.cuda.synchronize()))
     assert any(n.startswith("cdt_line") for n in names), names
-    assert np.array_equal(out.cpu().numpy(), edt_oracle.cdt(mask, nd, "chessboard", nthreads=16))
+    want = np.tile(chessboard(once), (reps,) + (1,) * nd)
+    assert np.array_equal(out.cpu().numpy(), want)
 
 
 # value and row in one key, and too large for one (11 bits of row beside 22 of value)
