@@ -537,7 +537,7 @@ __global__ void __launch_bounds__(256) k_scan_word(WordScanArgs a) {
             // store instruction then writes 1 KiB of it.
             const uint32_t rb = uint32_t(lw >> 1) * a.n + uint32_t(w) * WB + uint32_t(PKW / 2) * uint32_t(lw & 1);
 #pragma unroll
-            for (int k = 0; k < (PK ? WB / PKW : 0); ++k) {
+            for (int k = 0; k < (PK && lw < int(a.lpw) ? WB / PKW : 0); ++k) {
 #pragma unroll
                 for (int j = 0; j < PKW / 8; ++j) {
                     const int p0 = PKW * k + 8 * j;
@@ -555,8 +555,9 @@ __global__ void __launch_bounds__(256) k_scan_word(WordScanArgs a) {
             int4 *dst = reinterpret_cast<int4 *>(a.field_i + (blk * a.n1 + (l0 - blk * a.n1) / 2) * a.n);
 #pragma unroll
             for (int i = 0; i < WB / 8; ++i) {
+                // (words per line that do not divide 64 leave lanes without a row)
                 const int c = lane + kWave * i;
-                dst[c] = st[c + c / 8];
+                if (uint32_t(c) < a.lpw / 2u * a.n / 4u) dst[c] = st[c + c / 8];
             }
         }
         if (!PK) ds[lane] = live ? own : ~0ull;

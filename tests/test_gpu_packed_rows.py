@@ -1,7 +1,9 @@
 """GPU parity where the row scan's waves hold an odd number of rows (row widths
 of 384, 576 and 640: five and three rows per wave) and the extent of the next
 axis is a multiple of it: the packed row field pairs rows 2R and 2R + 1, which
-such waves cannot do, so the field has to go over unpacked."""
+such waves cannot do, so the field has to go over unpacked.  Widths of 448, 704
+and 768 leave lanes of a wave without a row (14, 22 and 24 words do not divide
+64); they must not write past the wave's rows."""
 import numpy as np
 import pytest
 
@@ -10,7 +12,7 @@ from oracle import edt_oracle
 
 pytestmark = pytest.mark.gpu
 
-CASES = [((130, 384), 2), ((66, 576), 3), ((129, 640), 6)]
+CASES = [((130, 384), 2), ((66, 576), 3), ((129, 640), 6), ((384, 448), 2), ((64, 768), 3), ((520, 704), 2)]
 
 
 @pytest.mark.parametrize("metric", ["euclidean", "taxicab", "chessboard"])
