@@ -171,8 +171,10 @@ def tm_edt(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None, out_idx
 
 def tm_edt_workspace_size(ndim: int, spatial, batch: int, sampling=None, with_indices=False) -> int:
     """Calls tm_edt_workspace_size: bytes of workspace tm_edt_ws uses (0: none)."""
-    return int(load().tm_edt_workspace_size(ndim, _shape_array(tuple([int(v) for v in spatial])), int(batch),
-                                            _sampling_array(sampling, ndim), 1 if with_indices else 0))
+    # exactly ndim extents: the library reads that many, however many are given
+    shape = (ctypes.c_int64 * ndim)(*[int(v) for v in spatial])
+    return int(load().tm_edt_workspace_size(ndim, shape, int(batch), _sampling_array(sampling, ndim),
+                                            1 if with_indices else 0))
 
 
 def tm_edt_ws(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None, out_idx=None,
@@ -285,8 +287,8 @@ def tm_cdt(in_u8: torch.Tensor, ndim: int, metric: int, out_dist, stream=None) -
 
 def tm_cdt_workspace_size(ndim: int, spatial, batch: int, metric: int) -> int:
     """Calls tm_cdt_workspace_size: bytes of workspace tm_cdt_ws uses (0: none)."""
-    return int(load().tm_cdt_workspace_size(ndim, _shape_array(tuple([int(v) for v in spatial])), int(batch),
-                                            int(metric)))
+    shape = (ctypes.c_int64 * ndim)(*[int(v) for v in spatial])
+    return int(load().tm_cdt_workspace_size(ndim, shape, int(batch), int(metric)))
 
 
 def tm_cdt_ws(in_u8: torch.Tensor, ndim: int, metric: int, out_dist, workspace=None, stream=None) -> None:

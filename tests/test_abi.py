@@ -166,6 +166,29 @@ def test_chamfer_workspace(lib):
     assert call(2, FAKE_IN + 64) == TM_ERR_ALIAS
 
 
+def test_workspace_size_takes_ndim_extents(lib, monkeypatch):
+    """The library reads ndim extents: with fewer given the rest are zeros
+    (refused: no workspace), with more the call raises."""
+    seen = []
+
+    class Library:
+        def __getattr__(self, name):
+            return lambda ndim, shape, *rest: seen.append((ndim, list(shape))) or 0
+    monkeypatch.setattr(binding, "load", Library)
+    assert binding.tm_edt_workspace_size(3, (512, 512), 32) == 0
+    assert binding.tm_cdt_workspace_size(3, (512, 512), 32, 2) == 0
+    assert seen == [(3, [512, 512, 0])] * 2
+    for size in (lambda *a: binding.tm_edt_workspace_size(*a), lambda *a: binding.tm_cdt_workspace_size(*a, 2)):
+        with pytest.raises(IndexError):
+            size(2, (4, 512, 512), 32)
+        with pytest.raises(ValueError):
+            size(-1, (), 32)
+    assert len(seen) == 2
+    monkeypatch.undo()
+    assert binding.tm_edt_workspace_size(3, (512, 512), 32) == 0
+    assert binding.tm_cdt_workspace_size(3, (512, 512), 32, 2) == 0
+
+
 def test_static_workspace_limit(lib):
     # tm_edt_noalloc refuses, on the host, requests whose dispatch order needs
     # more than its 64 KiB static workspace (8192 groups of 16 columns)
