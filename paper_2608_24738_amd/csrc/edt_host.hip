@@ -1008,12 +1008,15 @@ int run(Request &r) {
             if (p.lprag)
                 rc = fin ? launch("line_search_pair_final", k_line_pair16<true, false, true>, lgrid, lblock, p.lds, r.stream, lp)
                          : launch("line_search_pair", k_line_pair16<false, false, true>, lgrid, lblock, p.lds, r.stream, lp);
-            else if (pkw == 16 && a == nd - 2)
-                rc = fin ? launch("line_pair_final.i16", k_line_pair16<true, true>, lgrid, lblock, p.lds, r.stream, lp)
-                         : launch("line_pair.i16", k_line_pair16<false, true>, lgrid, lblock, p.lds, r.stream, lp);
-            else
-                rc = fin ? launch("line_pair_final", k_line_pair16<true>, lgrid, lblock, p.lds, r.stream, lp)
-                         : launch("line_pair", k_line_pair16<false>, lgrid, lblock, p.lds, r.stream, lp);
+            else {
+                const bool lpk = pkw == 16 && a == nd - 2;
+                const char *nm = fin ? (lpk ? "line_pair_final.i16" : "line_pair_final") : (lpk ? "line_pair.i16" : "line_pair");
+#define TM_LP(F, PK)                                                                                      \
+    (lwaves == 16 ? launch(nm, k_line_pair16<F, PK, false, true>, lgrid, lblock, p.lds, r.stream, lp)      \
+                  : launch(nm, k_line_pair16<F, PK>, lgrid, lblock, p.lds, r.stream, lp))
+                rc = fin ? (lpk ? TM_LP(true, true) : TM_LP(true, false)) : (lpk ? TM_LP(false, true) : TM_LP(false, false));
+#undef TM_LP
+            }
         } else if (p.bk) {
             BracketArgs ba{};
             ba.buf = index_path ? cidx : r.dist ? reinterpret_cast<int32_t *>(r.dist) : r.sq;

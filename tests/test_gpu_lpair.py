@@ -2,7 +2,7 @@
 lines of up to 512 rows per workgroup, two lines per packed 16-bit word),
 which unit-sampled distance passes take when their lines are a multiple of
 16 rows long, 16 neighbouring lines are adjacent in memory, and there are at
-least 512 groups of 16 lines.  Squared distances and distances must equal
+least 256 groups of 16 lines.  Squared distances and distances must equal
 the oracle's bit for bit.  The cases cover dense and sparse masks,
 workgroups whose lines hold at most 32 site rows (the direct minimum),
 distances of 256 and more with many site rows (the exact 32-bit re-search),
@@ -75,6 +75,23 @@ def test_long_distances_many_sites():
     mask[3, :41, 0] = 1
     mask[3, 500, 511] = 0          # one site row only: the direct minimum
     check(mask, 2, "long distances")
+
+
+# 480 rows: 15 waves per workgroup; 496 and 512: the form with 16 waves known
+# to the compiler.  Rows of 528 and 1040 go over as int32, 1024 packed; the
+# 3-D case runs it in the middle.
+@pytest.mark.parametrize("batch,spatial,expect", [
+    (8, (480, 1040), "line_pair_final"), (8, (496, 1040), "line_pair_final"), (8, (512, 528), "line_pair_final"),
+    (8, (480, 1024), "line_pair_final.i16"), (8, (496, 1024), "line_pair_final.i16"),
+    (1, (16, 496, 528), "line_pair"), (1, (16, 496, 512), "line_pair.i16")],
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_wave_counts(batch, spatial, expect):
+    rng = np.random.default_rng([36, batch, sum(spatial)])
+    mask = (rng.random((batch,) + spatial) >= 0.002).astype(np.uint8)
+    mask[0, ..., : spatial[-1] // 2] = 1               # long distances: the exact re-search
+    if batch > 1:
+        mask[1] = 1                                    # no background
+    check(mask, len(spatial), "wave counts", expect=(expect,))
 
 
 def test_samples_without_background():
