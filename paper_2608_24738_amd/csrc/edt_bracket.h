@@ -21,8 +21,8 @@
 // start on different banks.  Phases:
 //   1. near search (distance passes): patches of 16 rows by the windowed search
 //      in packed 16-bit arithmetic, which is the cheaper one up to about 48
-//      rows; patches with farther elements are left over (1 % background:
-//      none), and the workgroup ends here when none is;
+//      rows; patches with farther elements are left over, and the workgroup
+//      ends here when none is; when few are, they are searched on (to 249 rows);
 //   2. top anchors, one row in 64, searched outward by 8 lanes per line pair;
 //   3. anchors halfway, three levels down to one row in 8: the bracket between
 //      the two known neighbours, of which only the blocks of 8 rows are walked
@@ -70,6 +70,7 @@ constexpr int kTop = 8;                      // segments per top anchor
 constexpr int kBkRoots = 512;
 constexpr int kBkNear = 16;                  // rows of a near-search patch
 constexpr int kBkReach = 49;                 // distances the near search settles
+constexpr int kBkFewReach = 249;             // the same where few patches are farther
 
 enum BkMode : int { kBkField = 0, kBkDist = 1, kBkIndex = 2 };
 
@@ -103,7 +104,7 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
     static_assert(MODE != kBkIndex || (METRIC == kL2 && !PK), "index passes: euclidean, int32 carrier");
     constexpr int SH = MODE == kBkIndex ? 1 : 0;     // staged value = d << SH | sign
     extern __shared__ __attribute__((aligned(16))) uint16_t bk_tile[];
-    __shared__ uint32_t claim, claim_near, site_rows, far_count;
+    __shared__ uint32_t claim, claim_near, claim_few, site_rows, far_count, far_left;
     __shared__ uint32_t has_site[kBkLines];
     __shared__ uint64_t line_base[kBkLines];               // row 0 of each line
     __shared__ uint8_t far[kBkMaxN / kBkNear];             // patches the near search left over
@@ -143,6 +144,8 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
     if (t == 0) {
         claim = 0;
         claim_near = 0;
+        claim_few = 0;
+        far_left = 0;
         site_rows = 0;
         far_count = 0;
     }
@@ -281,48 +284,42 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
     // Elements within kBkReach of a site, patch by patch (16 rows x 16 lines):
     // the windowed search in packed 16-bit arithmetic, two lines per word and two
     // adjacent rows per lane, rows q - d and q + d at once.  A patch of which
-    // some element is farther is left to the brackets; it is given up early when
-    // its values after 8 steps say so.
+    // some element is farther is left over; it is given up early when its values
+    // after 8 steps say so.
     if constexpr (MODE != kBkIndex) {
         constexpr int kRowWords = kBkPitch / 2;
         const int jw = lane & 7, rho = lane >> 3;
         const uint32_t *const col = reinterpret_cast<const uint32_t *>(row0) + jw;
         const u16x2 on = {uint16_t(L0 + 2 * jw < a.lines ? 0xffff : 0), uint16_t(L0 + 2 * jw + 1 < a.lines ? 0xffff : 0)};
         const int nnear = (n + kBkNear - 1) / kBkNear, nq = (nnear + 3) / 4;
-        // euclidean: larger distances only have to stay large, and
-        // 250^2 + kBkReach^2 fits 16 bits
-        static_assert(250 * 250 + kBkReach * kBkReach < 65536, "near search: 16-bit values");
-        auto val = [](u16x2 e, int d) -> u16x2 {
-            if (METRIC == kLinf) return __builtin_elementwise_max(e, splat(d));
-            const u16x2 c = __builtin_elementwise_min(e, splat(250));
-            return c * c + splat(d * d);
+        // Patch p with steps up to kBkReach (FEW: kBkFewReach): true and its
+        // elements written, or false if one is farther.  Euclidean values past
+        // the reach only have to stay past its square: 250^2 + kBkReach^2 fits
+        // 16 bits (one multiply-add per step), FEW saturates.
+        static_assert(250 * 250 + (kBkReach + 4) * (kBkReach + 4) < 65536 && 255 * 255 >= kBkFewReach * kBkFewReach &&
+                          (kBkFewReach + 4) * (kBkFewReach + 4) < 65536,
+                      "near search: 16-bit values");
+        auto past = [](u16x2 m, int r) {                   // some value past distance r
+            return as_word(__builtin_elementwise_sub_sat(m, splat(METRIC == kLinf ? r : r * r))) != 0;
         };
-        for (int k = next(&claim_near); k < 4 * nq; k = next(&claim_near)) {
-            // four runs of rows in turn, so that the first patches sample the lines
-            const int p = (k & 3) * nq + (k >> 2);
-            if (p >= nnear) continue;
-            const int nfar = int(__builtin_amdgcn_readfirstlane(
-                __hip_atomic_load(&far_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
-            if (nfar >= 4 && 2 * nfar > k) {
-                // most patches so far were given up: this one is not tried
-                far[p] = 1;
-                continue;
-            }
+        auto settle = [&](int p, auto few) -> bool {
+            constexpr bool FEW = decltype(few)::value;
+            constexpr int reach = FEW ? kBkFewReach : kBkReach;
+            auto val = [](u16x2 e, int d) -> u16x2 {
+                if (METRIC == kLinf) return __builtin_elementwise_max(e, splat(d));
+                const u16x2 c = __builtin_elementwise_min(e, splat(FEW ? 255 : 250));
+                return FEW ? __builtin_elementwise_add_sat(c * c, splat(d * d)) : c * c + splat(d * d);
+            };
             const int q = kBkNear * p + 2 * rho, qc = min(q, n);      // (row n: guard)
-            u16x2 bA = val(as_pair(col[qc * kRowWords] ), 0) & on;
+            u16x2 bA = val(as_pair(col[qc * kRowWords]), 0) & on;
             u16x2 bB = val(as_pair(col[(qc + 1) * kRowWords]), 0) & on;
             if (q >= n) bA = splat(0);
             if (q + 1 >= n) bB = splat(0);
-            bool given_up = false;
 #pragma unroll 1
-            for (int d = 1; d < kBkReach; d += 4) {
-                const int reach = METRIC == kLinf ? d : d * d;
+            for (int d = 1; d < reach; d += 4) {
                 const u16x2 m = __builtin_elementwise_max(bA, bB);
-                if (__all(as_word(__builtin_elementwise_sub_sat(m, splat(reach))) == 0)) break;
-                if (d % 8 == 1 && d > 1) {
-                    given_up = __any(as_word(__builtin_elementwise_sub_sat(m, splat(METRIC == kLinf ? kBkReach - 1 : (kBkReach - 1) * (kBkReach - 1)))) != 0);
-                    if (given_up) break;
-                }
+                if (!__any(past(m, d))) break;
+                if (!FEW && d % 8 == 1 && d > 1 && __any(past(m, reach - 1))) return false;
                 const uint32_t *pl = col + max(qc - d - 3, -kBkG) * kRowWords;
                 const uint32_t *ph = col + min(qc + d, n + kBkG - 5) * kRowWords;
                 u16x2 U[5], W[5];
@@ -337,14 +334,7 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
                     bB = __builtin_elementwise_min(bB, val(__builtin_elementwise_min(U[4 - s], W[s + 1]), d + s));
                 }
             }
-            const int most = METRIC == kLinf ? kBkReach : kBkReach * kBkReach;
-            const u16x2 m = __builtin_elementwise_max(bA, bB);
-            const bool left = given_up || __any(as_word(__builtin_elementwise_sub_sat(m, splat(most))) != 0);
-            far[p] = left ? 1 : 0;
-            if (left) {
-                if (lane == 0) atomicAdd(&far_count, 1u);
-                continue;
-            }
+            if (__any(past(__builtin_elementwise_max(bA, bB), reach))) return false;
             const uint32_t h[4] = {bA.x, bA.y, bB.x, bB.y};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -358,9 +348,37 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
                     if (a.sq) a.sq[e] = int32_t(h[k]);
                 }
             }
+            return true;
+        };
+        for (int k = next(&claim_near); k < 4 * nq; k = next(&claim_near)) {
+            // four runs of rows in turn, so that the first patches sample the lines
+            const int p = (k & 3) * nq + (k >> 2);
+            if (p >= nnear) continue;
+            const int nfar = int(__builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(&far_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
+            // most patches so far were left over: this one is not tried
+            const bool left = (nfar >= 4 && 2 * nfar > k) || !settle(p, std::false_type{});
+            far[p] = left ? 1 : 0;
+            if (left && lane == 0) atomicAdd(&far_count, 1u);
         }
         __syncthreads();
-        if (far_count == 0) return;
+        const int nfar = int(far_count);
+        if (nfar == 0) return;
+        // A few patches left over (corners and gaps of a sparse background) are
+        // searched on: the brackets' phases are a chain whose length hardly
+        // depends on how many patches need them (1 % background: 8 x 1024^2 40
+        // -> 34 us per call, 9 x 900 x 800 48 -> 39 us, chessboard 37 -> 31 and 45
+        // -> 35 us; a limit of 1/2 instead of 1/4 loses 8 us on 8 x 1024^2 discs).
+        if (4 * nfar <= nnear) {
+            for (int p = next(&claim_few); p < nnear; p = next(&claim_few)) {
+                if (!__builtin_amdgcn_readfirstlane(int(far[p]))) continue;
+                const bool left = !settle(p, std::true_type{});
+                far[p] = left ? 1 : 0;
+                if (left && lane == 0) far_left = 1;
+            }
+            __syncthreads();
+            if (far_left == 0) return;
+        }
     }
 
     // ---- block minima and anchors ------------------------------------------------

@@ -2,7 +2,9 @@
 first strided pass, and the index pass of 2-D inputs with more than 256 rows.
 Masks put every phase to work: near patches only (dense), far ones (a few discs),
 few site rows (one pixel), no background, one background block in a corner (the
-longest brackets), all background.  Bit-exact against the oracle."""
+longest brackets), all background, a band without background a quarter of the
+lines long (few far patches, searched on; 2048 rows: past 249 rows, so left to the
+brackets after all).  Bit-exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -25,7 +27,9 @@ def masks(spatial, seed):
     one[tuple(rng.integers(0, n) for n in spatial)] = False
     corner = np.ones(spatial, bool)
     corner[tuple(slice(0, min(40, n)) for n in spatial)] = False
-    out += [far, one, np.ones(spatial, bool), corner, np.zeros(spatial, bool)]
+    band = out[0].copy()
+    band[..., spatial[-2] // 3 : spatial[-2] // 3 + spatial[-2] // 4 - 8, :] = True
+    out += [far, one, np.ones(spatial, bool), corner, np.zeros(spatial, bool), band]
     return np.stack(out).astype(np.uint8)
 
 
