@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
 #pragma unroll
                 for (int k = 0; k < MAXND; ++k) yy += c[k] * c[k];
                 zk[pos] = make_int4(c[0] << kBfKeyBits, c[1] << kBfKeyBits, MAXND > 2 ? c[MAXND - 1] << kBfKeyBits : 0,
-                                    (yy << kBfKeyBits) | int32_t(pos % kBfRun));
+                                    int32_t((uint32_t(yy) << kBfKeyBits) | pos % kBfRun));
             } else {
 #pragma unroll
                 for (int k = 0; k < MAXND; ++k)
@@ -182,11 +182,11 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
                     for (int j = 0; j < kBfPer; ++j) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            // (sums wrap modulo 2^32; the key itself fits)
-                            int32_t v = __mul24(x[j][0], y[i].x) + y[i].w;
-                            v = __mul24(x[j][1], y[i].y) + v;
-                            if (MAXND > 2) v = __mul24(x[j][MAXND - 1], y[i].z) + v;
-                            key[j] = min(key[j], v);
+                            // (unsigned: partial sums wrap modulo 2^32; the key itself fits)
+                            uint32_t v = uint32_t(__mul24(x[j][0], y[i].x)) + uint32_t(y[i].w);
+                            v = uint32_t(__mul24(x[j][1], y[i].y)) + v;
+                            if (MAXND > 2) v = uint32_t(__mul24(x[j][MAXND - 1], y[i].z)) + v;
+                            key[j] = min(key[j], int32_t(v));
                         }
                     }
                 }
