@@ -4,7 +4,7 @@
 // by visiting every background element of the sample.
 //
 // A workgroup owns kBfOut consecutive elements of one sample.  It walks the
-// sample's mask in chunks of kBfChunk bytes: the chunk's background
+// sample's mask in chunks of PB bytes per thread: the chunk's background
 // elements are compacted, in row-major order, into an LDS list of their
 // coordinates (scaled by the sampling when sampled), and every thread runs
 // the list against its elements, keeping the first strictly smaller value,
@@ -15,7 +15,8 @@
 // Two things bounded it on sparse masks (8 x 256^2, 1 % background: 163 us): 64
 // chunks of 1024 bytes per workgroup, each with ten background elements and three
 // barriers, and 32-bit multiplies (a quarter of the rate of 24-bit ones).
-// Chunks are now 4096 bytes for ranks 2 and 3, and unit euclidean transforms
+// Chunks are now 4096 bytes for ranks 2 and 3 (3072 for many workgroups of the
+// other forms), and unit euclidean transforms
 // whose squared extents sum to at most 2^21 (KEY) take
 //     d^2 - |x|^2 = |y|^2 - 2 x . y
 // with the list's number below it in one 32-bit key: one 24-bit multiply-add per
@@ -30,8 +31,15 @@ namespace tmedt {
 constexpr int kBfThreads = 256;
 constexpr int kBfPer = 4;                        // elements per thread
 constexpr int kBfOut = kBfThreads * kBfPer;      // elements per workgroup
-// mask bytes per thread and chunk (and so list entries per chunk), by rank
-__host__ __device__ constexpr int bf_bytes(int nd) { return nd > 0 ? 16 : 4; }
+// Mask bytes per thread and chunk (and so list entries per chunk and thread):
+// 16 for keys, and for ranks 2 and 3 while every workgroup runs at once (LDS holds
+// three of rank 2 per compute unit, two of rank 3); else 12, which leaves room
+// for five and three and loads four-byte words.  Sampled, us per call, with
+// chunks of 1024 bytes, 16 and 12 per thread: 16 x 24 x 40 x 41, 624 workgroups,
+// half background 2877, 3577, 2758, 1 % 108, 99, 75; 32 x 256^2, 2048 workgroups,
+// half background 7863, 8222, 7858; 8 x 256^2, 512 workgroups, 1 % 129, 75, 80.
+constexpr int kBfBytes = 16, kBfBytesMany = 12;
+__host__ constexpr bool bf_many(int nd, uint64_t groups) { return groups > 256u * (nd == 2 ? 3u : 2u); }
 constexpr int kBfKeyBits = 10;                   // KEY: bits of the number in a key
 constexpr int kBfRun = 1 << kBfKeyBits;          // KEY: list entries between two merges
 constexpr uint64_t kBfKeySum = uint64_t(1) << (31 - kBfKeyBits);   // KEY: most the squared extents sum to
@@ -48,16 +56,17 @@ struct BfArgs {
     double sd[kMaxDim];     // the same in double (virtual element)
 };
 
-template <int METRIC, bool SAMP, int ND, bool KEY = false>
+template <int METRIC, bool SAMP, int ND, bool KEY = false, int PB = (ND > 0) ? kBfBytes : 4>
 __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
     using V = typename std::conditional<SAMP, float, int32_t>::type;
     constexpr int MAXND = ND > 0 ? ND : kMaxDim;
     static_assert(!KEY || (METRIC == 0 && !SAMP && ND > 0), "keys: exact euclidean, rank 2 or 3");
-    constexpr int PB = bf_bytes(ND), kBfChunk = kBfThreads * PB;
+    static_assert(PB % 4 == 0 && kBfThreads * PB <= 65536, "16-bit offsets within a chunk");
+    constexpr int kBfChunk = kBfThreads * PB;
     __shared__ V zc[KEY ? 1 : kBfChunk][MAXND];   // background coordinates of the chunk
     // KEY: coordinates << kBfKeyBits and (sum of their squares << kBfKeyBits | number)
     __shared__ int4 zk[KEY ? kBfChunk + 4 : 1];
-    __shared__ uint32_t zflat[KEY ? 1 : kBfChunk];   // their flat indices
+    __shared__ uint16_t zflat[KEY ? 1 : kBfChunk];   // their flat indices less the chunk's first
     __shared__ uint32_t wave_tot[kBfThreads / kWave];
     const int nd = ND > 0 ? ND : a.ndim;
     const int t = threadIdx.x;
@@ -111,6 +120,9 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
             const uint32_t d4[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int j = 0; j < PB / 4; ++j) y.w[j] = d4[j];
+        } else if (p + PB <= a.vox && (uintptr_t(m) + p) % 4 == 0) {
+#pragma unroll
+            for (int j = 0; j < PB / 4; ++j) y.w[j] = reinterpret_cast<const uint32_t *>(m + p)[j];
         } else {
 #pragma unroll
             for (int j = 0; j < PB / 4; ++j) y.w[j] = 0;
@@ -163,7 +175,7 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
                 for (int k = 0; k < MAXND; ++k)
                     if (k < nd) zc[pos][k] = SAMP ? V(float(c[k]) * a.s[k]) : V(c[k]);
             }
-            if (!KEY) zflat[pos] = f;
+            if (!KEY) zflat[pos] = uint16_t(f - c0);
             ++pos;
         }
         if (KEY && t < 4) zk[count + t] = make_int4(0, 0, 0, 0x7fffffff);   // whole fours
@@ -232,7 +244,7 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
         // remember the winners' flat indices before the list is rewritten
 #pragma unroll
         for (int j = 0; j < kBfPer; ++j)
-            if (arg[j] != 0xffffffffu && arg[j] < 0x80000000u) arg[j] = 0x80000000u | zflat[arg[j]];
+            if (arg[j] != 0xffffffffu && arg[j] < 0x80000000u) arg[j] = 0x80000000u | (c0 + zflat[arg[j]]);
         __syncthreads();
     }
 

@@ -1415,9 +1415,13 @@ extern "C" int tm_dt_bf(const uint8_t *in_u8, int ndim, const int64_t *shape, in
     }
     const dim3 grid(uint32_t(x.bps * r.batch)), block(kBfThreads);
     const bool samp = !r.unit;
+    const bool many = bf_many(ndim, grid.x);
+#define TM_BF_ND(M, S, N)                                                                             \
+    (many ? launch("dt_bf", k_dt_bf<M, S, N, false, kBfBytesMany>, grid, block, 0, stream, x)          \
+          : launch("dt_bf", k_dt_bf<M, S, N>, grid, block, 0, stream, x))
 #define TM_BF(M, S)                                                                               \
-    (ndim == 2   ? launch("dt_bf", k_dt_bf<M, S, 2>, grid, block, 0, stream, x)                   \
-     : ndim == 3 ? launch("dt_bf", k_dt_bf<M, S, 3>, grid, block, 0, stream, x)                   \
+    (ndim == 2   ? TM_BF_ND(M, S, 2)                                                              \
+     : ndim == 3 ? TM_BF_ND(M, S, 3)                                                              \
                  : launch("dt_bf", k_dt_bf<M, S, 0>, grid, block, 0, stream, x))
     // exact euclidean: value and number in one key while the squared extents allow
     uint64_t sumsq = 0;
@@ -1429,6 +1433,7 @@ extern "C" int tm_dt_bf(const uint8_t *in_u8, int ndim, const int64_t *shape, in
     else if (metric == TM_METRIC_TAXICAB) rc = samp ? TM_BF(1, true) : TM_BF(1, false);
     else rc = samp ? TM_BF(2, true) : TM_BF(2, false);
 #undef TM_BF
+#undef TM_BF_ND
     return rc;
 }
 

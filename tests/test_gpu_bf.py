@@ -87,6 +87,19 @@ def test_bf_parity(metric, shape, ndim, p_bg):
     check(mask, ndim, metric, samp, "sampled")
 
 
+# more workgroups than run at once (768 of rank 2, 512 of rank 3): chunks of 3072
+# bytes, two per sample, of samples at every alignment
+@pytest.mark.parametrize("metric", METRICS)
+@pytest.mark.parametrize("shape,ndim", [((200, 67, 61), 2), ((120, 13, 17, 19), 3)], ids=["2d", "3d"])
+def test_bf_many_workgroups(metric, shape, ndim):
+    mask = rand_mask(shape, 0.03, sum(shape))
+    mask[0] = 0                      # all background: a full list
+    mask[1] = 1
+    if metric != "euclidean":        # (unit euclidean takes keys)
+        check(mask, ndim, metric, None, "many")
+    check(mask, ndim, metric, [0.5 + 0.4 * a for a in range(ndim)], "many sampled")
+
+
 @pytest.mark.parametrize("metric", METRICS)
 def test_bf_degenerate(metric):
     shape = (3, 17, 19)
