@@ -101,11 +101,13 @@ int tm_edt(const uint8_t *in_u8, int ndim, const int64_t *shape, int64_t batch,
  * regions some groups of lines carry several times the mean work; run last,
  * they set the end of the pass.  With a workspace, a 2-D distance request
  * (unit sampling, no indices) whose column pass runs at least 1024
- * workgroups of 16 columns (rows of at most 512) or of 8 columns (longer
- * rows, ordered in units of four such workgroups) has its row pass estimate
- * each group's work, a one-workgroup kernel order the groups heaviest first,
- * and the column pass dispatch them in that order.  Results are identical to tm_edt's, bit for bit: the order
- * decides only when each group runs.
+ * workgroups of 16 columns (columns of at most 512 rows) or of 8 columns
+ * (longer ones, ordered in units of four such workgroups) has its row pass
+ * estimate each group's work, a one-workgroup kernel order the groups heaviest
+ * first, and the column pass dispatch them in that order.  Columns whose pass
+ * evens out its own work (1024 x 1024 images among them) keep no order.
+ * Results are identical to tm_edt's, bit for bit: the order decides only when
+ * each group runs.
  *
  *   workspace        NULL, or a DEVICE pointer, 4-byte aligned, owned by the
  *                    caller and not overlapping the input or outputs.
@@ -269,8 +271,8 @@ int tm_cdt(const uint8_t *in_u8, int ndim, const int64_t *shape, int64_t batch, 
  * chessboard request's column pass (at least 1024 workgroups of 8 columns,
  * ordered in units of four of them) keeps a heaviest-first dispatch order, as
  * tm_edt_ws does for the exact transform; results are identical to tm_cdt's.
- * Taxicab whole-line passes do the same work on every group and take no
- * workspace (size 0).
+ * Taxicab whole-line passes, and the longer columns that tm_edt_ws does not
+ * order either, take no workspace (size 0).
  * workspace and workspace_bytes as for tm_edt_ws; tm_cdt_workspace_size()
  * gives the bytes a request uses (8 per unit of 32 columns, or 0; host only).
  * Errors: as tm_cdt, plus TM_ERR_WORKSPACE and TM_ERR_ALIAS as for tm_edt_ws.

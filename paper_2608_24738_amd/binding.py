@@ -210,18 +210,13 @@ def tm_edt_noalloc(in_u8: torch.Tensor, ndim: int, sampling=None, out_dist=None,
 # Workspaces of the scipy-style wrapper, one per (device, stream): calls on one
 # stream run in order, so they can share it.
 _workspaces = {}
-# Columns of these lengths, in rows at least this wide, take the bracketed search,
-# whose groups gain nothing from a dispatch order: 8 x 1024^2 discs 66 us per call
-# without, 72 us with one.
-_UNORDERED_ROWS = range(896, 2049)
-_UNORDERED_WIDTH = 512
 
 
 @functools.lru_cache(maxsize=1024)
 def _order_bytes(entry: str, spatial: tuple, batch: int) -> int:
     """Workspace the wrappers keep for a unit-sampled distance request: only
     2-D column passes keep an order."""
-    if len(spatial) != 2 or (spatial[0] in _UNORDERED_ROWS and spatial[1] >= _UNORDERED_WIDTH):
+    if len(spatial) != 2:
         return 0
     if entry == "tm_cdt":
         return tm_cdt_workspace_size(2, spatial, batch, METRICS["chessboard"])

@@ -87,7 +87,6 @@ struct BracketArgs {
     int32_t coords;        // kBkIndex: write the coordinate slices at buf
     uint32_t kbits;        // KEY: bits of the row in a key
     uint32_t fcap;         // KEY: value of rows without sites
-    const uint32_t *order; // null, or the order of the units of two workgroups (k_order)
 };
 
 __host__ __device__ constexpr uint32_t bk_segs(uint32_t n, int s) { return (n + uint32_t(s) - 1) / uint32_t(s); }
@@ -122,13 +121,9 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
 
     // Two consecutive groups of 16 lines share each 128-byte line of a row:
     // they go to the workgroups b and b + 8, which the dispatcher sends to one
-    // XCD (one L2), in order of the schedule's units of two when there is one
-    // (the grid is then a multiple of 16).
+    // XCD (one L2).
     uint32_t g = blockIdx.x;
-    if (a.order) {
-        const uint32_t x = g & 7u, i = g >> 3;
-        g = 2u * a.order[(i >> 1) * 8u + x] + (i & 1u);
-    } else if (g < (gridDim.x & ~15u)) {
+    if (g < (gridDim.x & ~15u)) {
         const uint32_t x = g & 7u, i = g >> 3;
         g = (i >> 1) * 16u + x * 2u + (i & 1u);
     }

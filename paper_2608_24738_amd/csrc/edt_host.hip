@@ -623,7 +623,8 @@ constexpr uint64_t kOrderMinGroups = 1024;
 // whole workgroups of the scan inside one sample, at most 256 groups per row,
 // at least kOrderMinGroups workgroups and at most kOrderMax groups.  groups =
 // 0: none.  (On 3-D inputs the packed passes measured no faster in cost
-// order.)
+// order, nor does k_line_bracket, all of whose workgroups run at once: 8 x
+// 1024^2 discs 66 us per call without an order, 72 us with one.)
 struct OrderPlan {
     uint64_t groups;
     uint32_t width;
@@ -633,7 +634,7 @@ OrderPlan order_groups(const Request &r, const FhPlan *fh, uint64_t total) {
     if (r.ndim != 2 || !r.unit || r.big || r.idx || r.sgn) return {0, 0};
     // k_line_search orders units of four groups of 8 lines (32 columns)
     const uint32_t width = (fh[0].lp16 && r.metric == kL2) ? uint32_t(kLpLines)
-                           : (!fh[0].tiled16 && !fh[0].l1long && !fh[0].lprag && (fh[0].ls_lpw == 8 || fh[0].bk)) ? 32u : 0u;
+                           : (!fh[0].tiled16 && !fh[0].l1long && !fh[0].lprag && fh[0].ls_lpw == 8) ? 32u : 0u;
     if (!width) return {0, 0};
     const uint32_t n0 = r.shape[0], nlast = r.shape[1];
     if (nlast % kWave != 0 || nlast > uint32_t(kWave * kWave) || nlast / width > 256) return {0, 0};
@@ -840,8 +841,7 @@ int run(Request &r) {
                     else rc = TM_WORD(kScanFieldInt);
                     break;
                 case kScanFieldL1:
-                    if (order_n && pkw == 16) rc = TM_WORD_X("scan_word.cost.o16", kScanFieldL1, 32, 16);
-                    else if (order_n && pkw) rc = TM_WORD_X("scan_word.cost.o16", kScanFieldL1, 32, 8);
+                    if (order_n && pkw) rc = TM_WORD_X("scan_word.cost.o16", kScanFieldL1, 32, 8);
                     else if (order_n) rc = TM_WORD_X("scan_word.cost", kScanFieldL1, 32, 0);
                     else if (pkw == 16) rc = TM_WORD_X("scan_word.o16", kScanFieldL1, 0, 16);
                     else if (pkw) rc = TM_WORD_X("scan_word.o16", kScanFieldL1, 0, 8);
@@ -1032,7 +1032,6 @@ int run(Request &r) {
             ba.kbits = p.rbits;
             ba.fcap = p.fcap;
             const dim3 bgrid(uint32_t((lines + kBkLines - 1) / kBkLines));
-            if (order_n && a == 0 && bgrid.x == 2 * order_n) ba.order = r.ws + order_n;
             // a wave per 4 segments of 16 lines, at most 16 waves
             const uint32_t patches = (bk_segs(n, kBkSeg) + 3) / 4;
             const dim3 bblock(kWave * std::min(patches, 16u));

@@ -136,7 +136,8 @@ def test_workspace_size(lib):
     assert size(2, (512, 512), 32) == 8 * 32 * 512 // 16
     assert size(2, (512, 512), 32, (1.0, 1.0)) == 8 * 1024          # unit sampling spelled out
     assert size(2, (128, 512), 32) == 8 * 32 * 512 // 16            # 32-position row words
-    assert size(2, (1024, 1024), 8) == 8 * 8 * 1024 // 32           # whole-line search: units of 4 x 8 lines
+    assert size(2, (768, 512), 16) == 8 * 16 * 512 // 32            # whole-line search: units of 4 x 8 lines
+    assert size(2, (1024, 1024), 8) == 0                             # bracketed search: keeps no order
     assert size(2, (512, 512), 512) == 8 * 16384                     # the most groups one order holds
     assert size(2, (512, 512), 16) == 0                              # 512 groups: no order
     assert size(2, (512, 512), 32, None, True) == 0                  # indices: other passes
@@ -152,7 +153,8 @@ def test_workspace_size(lib):
 
 def test_chamfer_workspace(lib):
     size = binding.tm_cdt_workspace_size
-    assert size(2, (1024, 1024), 8, 2) == 8 * 8 * 1024 // 32        # units of four 8-column workgroups
+    assert size(2, (512, 512), 32, 2) == 8 * 32 * 512 // 32         # units of four 8-column workgroups
+    assert size(2, (1024, 1024), 8, 2) == 0                          # bracketed search: keeps no order
     assert size(2, (1024, 1024), 8, 1) == 0                          # taxicab: prefix minima, even work
     assert size(2, (256, 256), 8, 2) == 0                            # 256 workgroups: no order
     assert size(3, (64, 64, 64), 8, 2) == 0

@@ -195,25 +195,12 @@ def test_rejects_euclidean_and_unknown_metrics():
             binding.tm_cdt(x, 2, code, out)
 
 
-@pytest.mark.parametrize("metric", ["chessboard"])
-def test_ordered_column_pass(metric):
-    """tm_cdt_ws (chessboard): the column pass of 8 x 1024^2 discs dispatched heaviest
-    first from the row scan's estimates (units of four 8-column workgroups):
-    equal to tm_cdt, the chamfer equations at every element and brute-force
-    values at seeded points (as the full-size test), counters cleared, the
-    order a permutation."""
+def run_cdt_ws(mask, code, ws):
+    """tm_cdt_ws on (batch, n0, n1) ``mask``; returns (distances, kernel names)."""
     import torch
     from paper_2608_24738_amd import binding
-    dev = torch.device("cuda:0")
-    mask = workloads.make_mask(7)[:, 0].copy()
-    mask[5] = 1                                     # a sample without background: -1
-    announce("cdt ordered %s shape=%s" % (metric, mask.shape))
-    code = binding.METRICS[metric]
-    need = binding.tm_cdt_workspace_size(2, mask.shape[1:], mask.shape[0], code)
-    assert need > 0
-    x = torch.from_numpy(mask).to(dev)
-    ws = torch.zeros(need // 4, dtype=torch.int32, device=dev)
-    out = torch.empty(mask.shape, dtype=torch.int32, device=dev)
+    x = torch.from_numpy(np.ascontiguousarray(mask)).cuda()
+    out = torch.empty(mask.shape, dtype=torch.int32, device=x.device)
     binding.prof_enable(64)
     try:
         binding.tm_cdt_ws(x, 2, code, out, ws)
@@ -221,22 +208,50 @@ def test_ordered_column_pass(metric):
         names = [n for n, _ in binding.prof_read()]
     finally:
         binding.prof_enable(0)
+    return out.cpu().numpy(), names
+
+
+def test_ordered_column_pass():
+    """tm_cdt_ws (chessboard): the column pass of 32 x 512^2 discs dispatched
+    heaviest first from the row scan's estimates (units of four 8-column
+    workgroups): equal to tm_cdt, to the chamfer equations at every element and
+    to brute-force values at seeded points, counters cleared, the order a
+    permutation."""
+    import torch
+    from paper_2608_24738_amd import binding
+    mask = workloads.make_mask(2)[:, 0].copy()
+    mask[5] = 1                                     # a sample without background: -1
+    announce("cdt ordered shape=%s" % (mask.shape,))
+    code = binding.METRICS["chessboard"]
+    need = binding.tm_cdt_workspace_size(2, mask.shape[1:], mask.shape[0], code)
+    assert need > 0
+    ws = torch.zeros(need // 4, dtype=torch.int32, device="cuda:0")
+    got, names = run_cdt_ws(mask, code, ws)
     assert names == ["scan_word.cost.o16", "order", "cdt_line_final.i16"], names
-    got = out.cpu().numpy()
-    assert np.array_equal(got, run_cdt(mask, 2, metric))
-    assert (got[5] == -1).all()
-    rng = np.random.default_rng([7, 6])
-    for b in range(mask.shape[0]):
-        if b == 5:
-            continue
-        assert chamfer_fixed_point_violations(mask[b], got[b], metric) == 0, b
-        pts = np.stack([rng.integers(0, n, 64) for n in mask.shape[1:]], axis=1)
-        ref = edt_oracle.metric_dt_at(mask[b], metric, pts)
-        assert np.array_equal(got[b][tuple(pts.T)], ref.astype(np.int64)), b
+    assert np.array_equal(got, run_cdt(mask, 2, "chessboard"))
+    full_size_checks(mask, got, "chessboard", 2)
     w = ws.cpu().numpy()
     units = need // 8
     assert not w[:units].any()
     assert np.array_equal(np.sort(w[units:2 * units]), np.arange(units))
+
+
+def test_bracketed_column_pass_keeps_no_order():
+    """tm_cdt_ws (chessboard) of 8 x 1024^2 discs: no workspace used, equal to
+    tm_cdt, to the chamfer equations and to brute-force values as above."""
+    import torch
+    from paper_2608_24738_amd import binding
+    mask = workloads.make_mask(7)[:, 0].copy()
+    mask[5] = 1                                     # a sample without background: -1
+    announce("cdt bracketed shape=%s" % (mask.shape,))
+    code = binding.METRICS["chessboard"]
+    assert binding.tm_cdt_workspace_size(2, mask.shape[1:], mask.shape[0], code) == 0
+    ws = torch.arange(512, dtype=torch.int32, device="cuda:0")
+    got, names = run_cdt_ws(mask, code, ws)
+    assert names == ["scan_word.o16", "cdt_line_final.i16"], names
+    assert np.array_equal(ws.cpu().numpy(), np.arange(512))
+    assert np.array_equal(got, run_cdt(mask, 2, "chessboard"))
+    full_size_checks(mask, got, "chessboard", 7)
 
 
 def full_size_checks(mask, got, metric, key):

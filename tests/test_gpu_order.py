@@ -3,7 +3,7 @@ column pass of 2-D distance requests with at least 1024 groups of columns:
 the row scan estimates each group's work (k_scan_word with the cost
 estimate), k_order sorts the groups heaviest first, and the column pass
 (k_line_pair16, 16 columns per workgroup, or k_line_search, 8) takes them in
-that order.  The
+that order; k_line_bracket keeps none.  The
 order decides only when each group runs, so every result must equal the
 oracle's bit for bit, and equal tm_edt's (no workspace), whatever the
 workspace held before the call.  Each case checks which kernels ran.
@@ -93,18 +93,36 @@ def test_short_batch_32_position_words():
     check_ordered(mask, "32x128x512")
 
 
-def test_whole_line_search_full_workload_9():
-    # 8 x 1024^2 discs: columns of 1024 rows, 8 per workgroup of k_line_search
-    mask = workloads.make_mask(9)[:, 0]
-    check_ordered(mask, "8x1024^2 discs", final="line_search_final.i16")
+def test_whole_line_search_discs():
+    # 16 x 768 x 512 discs: columns of 768 rows, 8 per workgroup of k_line_search
+    mask = workloads.make_mask(9, (768, 512), 16)[:, 0]
+    check_ordered(mask, "16x768x512 discs", final="line_search_final.i16")
 
 
 @pytest.mark.parametrize("p_bg", [0.01, 0.0002])
 def test_whole_line_search_densities(p_bg):
     rng = np.random.default_rng([45, int(p_bg * 1e4)])
-    mask = (rng.random((8, 1024, 1024)) >= p_bg).astype(np.uint8)
+    mask = (rng.random((16, 768, 512)) >= p_bg).astype(np.uint8)
     mask[3] = 1                      # no background: the virtual element
-    check_ordered(mask, "1024^2 p_bg=%g" % p_bg, final="line_search_final.i16")
+    check_ordered(mask, "768x512 p_bg=%g" % p_bg, final="line_search_final.i16")
+
+
+@pytest.mark.parametrize("p_bg", [None, 0.01, 0.0002])
+def test_bracketed_search_keeps_no_order(p_bg):
+    # 8 x 1024^2: no workspace asked for, and one that is given stays as it was
+    if p_bg is None:
+        mask = workloads.make_mask(9)[:, 0].copy()
+    else:
+        mask = (np.random.default_rng([46, int(p_bg * 1e4)]).random((8, 1024, 1024)) >= p_bg).astype(np.uint8)
+    mask[3] = 1                      # no background: the virtual element
+    announce("no order shape=%s p_bg=%s" % (mask.shape, p_bg))
+    junk = np.arange(512, dtype=np.uint32)
+    dist, names, ws, need = run_ws(mask, ws_fill=junk, ws_bytes=2048)
+    assert need == 0
+    assert names == ["scan_word.o16", "line_search_final.i16"], names
+    assert np.array_equal(ws.view(np.uint32), junk)
+    ora = edt_oracle.edt(mask, 2, None, want_sq=False, want_dist=True, nthreads=16)
+    check_against_oracle(mask, 2, None, {"dist": dist}, ora)
 
 
 def test_samples_without_background_and_ties():

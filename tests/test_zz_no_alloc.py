@@ -63,14 +63,15 @@ def test_noalloc_matches_workspace_entry():
 
 def test_noalloc_whole_line_search_order():
     """The order of the whole-line search (units of four 8-column workgroups)
-    in the static workspace: 8 x 1024^2 discs, then a smaller 4 x 768 x 2048
-    input, each equal to tm_edt_ws's result."""
+    in the static workspace: 16 x 768 x 512 discs, a 4 x 768 x 2048 input, and
+    8 x 1024^2, whose bracketed search keeps none; each equal to tm_edt_ws's
+    result and to the oracle's."""
     import torch
     from paper_2608_24738_amd import binding
     lib = binding.load()
     dev = torch.device("cuda:0")
     stream = torch.cuda.current_stream().cuda_stream
-    for spatial, batch in [((1024, 1024), 8), ((768, 2048), 4)]:
+    for spatial, batch, ordered in [((768, 512), 16, True), ((768, 2048), 4, True), ((1024, 1024), 8, False)]:
         mask = workloads.make_mask(9, spatial, batch)[:, 0].copy()
         x = torch.from_numpy(mask).to(dev)
         announce("tm_edt_noalloc whole-line search shape=%s" % (mask.shape,))
@@ -84,10 +85,14 @@ def test_noalloc_whole_line_search_order():
             binding.prof_enable(0)
         assert rc == 0, binding.tm_strerror(rc)
         need = binding.tm_edt_workspace_size(2, spatial, batch)
-        assert need > 0
-        assert names == ["scan_word.cost.o16", "order", "line_search_final.i16"], names
+        assert (need > 0) == ordered
+        assert names == (["scan_word.cost.o16", "order", "line_search_final.i16"] if ordered
+                         else ["scan_word.o16", "line_search_final.i16"]), names
         ws = torch.zeros(max(1, need // 4), dtype=torch.int32, device=dev)
         ref = torch.empty_like(out)
         binding.tm_edt_ws(x, 2, None, ref, None, ws)
         torch.cuda.synchronize()
-        assert np.array_equal(out.cpu().numpy(), ref.cpu().numpy())
+        got = out.cpu().numpy()
+        assert np.array_equal(got, ref.cpu().numpy())
+        ora = edt_oracle.edt(mask, 2, None, want_sq=False, want_dist=True, nthreads=16)
+        check_against_oracle(mask, 2, None, {"dist": got}, ora)
