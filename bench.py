@@ -77,17 +77,18 @@ def algorithmic_bytes(name, total, ndim, want_idx, out_bytes=4):
     if base == "plane_signed_final":         # those bytes in, signed distances out
         return total * (1 + out_bytes)
     if base in ("fh_field", "tile_pair", "cdt_pair", "cdt_line", "cdt_none",
-                "line_search", "line_search_signed", "line_pair", "cdt_l1_scan"):
+                "line_search", "line_search_signed", "line_pair", "line_pair_rag", "line_bracket",
+                "cdt_bracket", "cdt_l1_scan"):
         return total * (fin + fout)
     if base in ("fh_field_final", "tile_pair_final", "cdt_pair_final", "cdt_line_final",
                 "line_search_final", "plane_final", "line_search_signed_final", "line_pair_final",
-                "cdt_l1_scan_final"):
+                "line_pair_rag_final", "line_bracket_final", "cdt_bracket_final", "cdt_l1_scan_final"):
         return total * (fin + out_bytes)
     if base == "small2d":                    # mask in; distances (and indices) out
         return total * (1 + out_bytes + (4 * ndim if want_idx else 0))
     if base in ("fh_index", "tile_idx", "fh_long"):     # flat-index carrier in and out
         return total * (4 + 4)
-    if base in ("fh_index_final", "tile_idx_final", "fh_long_final"):
+    if base in ("fh_index_final", "tile_idx_final", "fh_long_final", "line_bracket_idx_final"):
         # carrier in; coordinates (with indices) and distances out
         return total * (4 + (4 * ndim if want_idx else 0) + out_bytes)
     if base == "order":                      # 8 bytes per group of 16 lines: not counted

@@ -1006,8 +1006,8 @@ int run(Request &r) {
             const dim3 lgrid(uint32_t((lines + kLpLines - 1) / kLpLines)), lblock(kWave * lwaves);
             if (order_n && a == 0 && lgrid.x == order_n) lp.order = r.ws + order_n;
             if (p.lprag)
-                rc = fin ? launch("line_search_pair_final", k_line_pair16<true, false, true>, lgrid, lblock, p.lds, r.stream, lp)
-                         : launch("line_search_pair", k_line_pair16<false, false, true>, lgrid, lblock, p.lds, r.stream, lp);
+                rc = fin ? launch("line_pair_rag_final", k_line_pair16<true, false, true>, lgrid, lblock, p.lds, r.stream, lp)
+                         : launch("line_pair_rag", k_line_pair16<false, false, true>, lgrid, lblock, p.lds, r.stream, lp);
             else {
                 const bool lpk = pkw == 16 && a == nd - 2;
                 const char *nm = fin ? (lpk ? "line_pair_final.i16" : "line_pair_final") : (lpk ? "line_pair.i16" : "line_pair");
@@ -1038,18 +1038,18 @@ int run(Request &r) {
             const bool bpk = pkw == 16;
 #define TM_BK(NM, ...) launch(NM, k_line_bracket<__VA_ARGS__, kBkSeg>, bgrid, bblock, p.lds, r.stream, ba)
             if (index_path)
-                rc = p.bk_key ? TM_BK("line_search_idx_final", kL2, kBkIndex, false, true)
-                              : TM_BK("line_search_idx_final", kL2, kBkIndex, false, false);
+                rc = p.bk_key ? TM_BK("line_bracket_idx_final", kL2, kBkIndex, false, true)
+                              : TM_BK("line_bracket_idx_final", kL2, kBkIndex, false, false);
             else if (r.metric == kLinf)
-                rc = fin ? (bpk ? TM_BK("cdt_line_final.i16", kLinf, kBkDist, true, false)
-                                : TM_BK("cdt_line_final", kLinf, kBkDist, false, false))
-                         : (bpk ? TM_BK("cdt_line.i16", kLinf, kBkField, true, false)
-                                : TM_BK("cdt_line", kLinf, kBkField, false, false));
+                rc = fin ? (bpk ? TM_BK("cdt_bracket_final.i16", kLinf, kBkDist, true, false)
+                                : TM_BK("cdt_bracket_final", kLinf, kBkDist, false, false))
+                         : (bpk ? TM_BK("cdt_bracket.i16", kLinf, kBkField, true, false)
+                                : TM_BK("cdt_bracket", kLinf, kBkField, false, false));
             else
-                rc = fin ? (bpk ? TM_BK("line_search_final.i16", kL2, kBkDist, true, false)
-                                : TM_BK("line_search_final", kL2, kBkDist, false, false))
-                         : (bpk ? TM_BK("line_search.i16", kL2, kBkField, true, false)
-                                : TM_BK("line_search", kL2, kBkField, false, false));
+                rc = fin ? (bpk ? TM_BK("line_bracket_final.i16", kL2, kBkDist, true, false)
+                                : TM_BK("line_bracket_final", kL2, kBkDist, false, false))
+                         : (bpk ? TM_BK("line_bracket.i16", kL2, kBkField, true, false)
+                                : TM_BK("line_bracket", kL2, kBkField, false, false));
 #undef TM_BK
         } else if (p.l1scan) {
             LineSearchArgs la{};

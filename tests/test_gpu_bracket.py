@@ -44,8 +44,10 @@ def names_of(fn):
 
 
 # rows at the rule's edges (640, and 896 for rows of a multiple of 64, which go over
-# packed), one segment short and over, partial last groups, the longest line
-SHAPES = [(640, 513), (647, 515), (897, 576), (1024, 512), (2048, 517), (3, 645, 521)]
+# packed where a scan wave's rows pair up), one segment short and over, partial last
+# groups, the longest line; the middle axis of 3-D inputs
+SHAPES = [((640, 513), ""), ((647, 515), ""), ((897, 576), ""), ((1024, 512), ".16"), ((2048, 517), ""),
+          ((3, 645, 521), ""), ((2, 900, 512), ".16")]
 
 
 def chessboard(mask):
@@ -63,8 +65,8 @@ def chessboard(mask):
     return torch.where(f < (1 << 20), f, -1).cpu().numpy()
 
 
-@pytest.mark.parametrize("spatial", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
-def test_distances(spatial):
+@pytest.mark.parametrize("spatial,packed", SHAPES, ids=["x".join(map(str, s)) for s, _ in SHAPES])
+def test_distances(spatial, packed):
     import torch
 
     from paper_2608_24738_amd import binding
@@ -74,15 +76,17 @@ def test_distances(spatial):
     reps = -(-512 * 16 * spatial[-2] // once.size) + 1
     mask = np.tile(once, (reps,) + (1,) * nd)
     announce("bracket distances shape=%s" % (mask.shape,))
+    kernel = "bracket" + ("_final" if nd == 2 else "") + packed.replace(".", ".i")
     res, names = names_of(lambda: run_gpu(mask, nd, None, dist=True, idx=False, sq=True))
-    assert any(n.startswith("line_search") for n in names), names
+    assert "line_" + kernel in names, names
+    assert ("scan_word.o16" in names) == bool(packed), names
     ora = edt_oracle.edt(once, nd, None, nthreads=16)
     ora = {k: np.tile(ora[k], (reps,) + (1,) * nd) for k in ("dist", "sq")}
     check_against_oracle(mask, nd, None, res, ora)
     x = torch.from_numpy(mask).cuda()
     out = torch.empty(mask.shape, dtype=torch.int32, device=x.device)
     _, names = names_of(lambda: (binding.tm_cdt(x, nd, 2, out), torch.cuda.synchronize()))
-    assert any(n.startswith("cdt_line") for n in names), names
+    assert "cdt_" + kernel in names, names
     want = np.tile(chessboard(once), (reps,) + (1,) * nd)
     assert np.array_equal(out.cpu().numpy(), want)
 
@@ -94,7 +98,38 @@ def test_indices(spatial):
     mask = masks(spatial, sum(spatial) + 1)
     announce("bracket indices shape=%s" % (mask.shape,))
     res, names = names_of(lambda: run_gpu(mask, 2, None, dist=True, idx=True))
-    assert "line_search_idx_final" in names, names
+    assert "line_bracket_idx_final" in names, names
     check_against_oracle(mask, 2, None, res, edt_oracle.edt(mask, 2, None, nthreads=16))
     only, _ = names_of(lambda: run_gpu(mask, 2, None, dist=False, idx=True))
     assert np.array_equal(only["idx"], res["idx"])
+
+
+def test_widest_rows():
+    """Rows of 16000, lines of 2048 (the rule's largest): one background block of 40
+    x 40 in a corner, so that values reach the largest a key and a 16-bit distance
+    hold.  Its nearest element is known in closed form."""
+    import torch
+
+    from paper_2608_24738_amd import binding
+    n, w = 2048, 16000
+    dev = torch.device("cuda:0")
+    x = torch.ones((1, n, w), dtype=torch.uint8, device=dev)
+    x[0, :40, :40] = 0
+    r, c = torch.arange(n, device=dev)[:, None], torch.arange(w, device=dev)[None]
+    dr, dc = (r - 39).clamp(min=0), (c - 39).clamp(min=0)
+    sq = (dr * dr + dc * dc).to(torch.int32)
+    announce("bracket widest rows 1x%dx%d" % (n, w))
+    out = torch.empty((1, n, w), dtype=torch.int32, device=dev)
+    _, names = names_of(lambda: (binding.tm_edt_sq(x, 2, out), torch.cuda.synchronize()))
+    assert "line_bracket_final" in names, names
+    assert torch.equal(out[0], sq)
+    _, names = names_of(lambda: (binding.tm_cdt(x, 2, 2, out), torch.cuda.synchronize()))
+    assert "cdt_bracket_final" in names, names
+    assert torch.equal(out[0], torch.maximum(dr, dc).to(torch.int32))
+    dist = torch.empty((1, n, w), dtype=torch.float32, device=dev)
+    idx = torch.empty((1, 2, n, w), dtype=torch.int32, device=dev)
+    _, names = names_of(lambda: (binding.tm_edt(x, 2, None, dist, idx), torch.cuda.synchronize()))
+    assert "line_bracket_idx_final" in names, names
+    assert torch.equal(dist[0], sq.double().sqrt().float())
+    assert torch.equal(idx[0, 0], r.clamp(max=39).expand(n, w).to(torch.int32))
+    assert torch.equal(idx[0, 1], c.clamp(max=39).expand(n, w).to(torch.int32))

@@ -248,7 +248,7 @@ def test_bracketed_column_pass_keeps_no_order():
     assert binding.tm_cdt_workspace_size(2, mask.shape[1:], mask.shape[0], code) == 0
     ws = torch.arange(512, dtype=torch.int32, device="cuda:0")
     got, names = run_cdt_ws(mask, code, ws)
-    assert names == ["scan_word.o16", "cdt_line_final.i16"], names
+    assert names == ["scan_word.o16", "cdt_bracket_final.i16"], names
     assert np.array_equal(ws.cpu().numpy(), np.arange(512))
     assert np.array_equal(got, run_cdt(mask, 2, "chessboard"))
     full_size_checks(mask, got, "chessboard", 7)

@@ -12,7 +12,7 @@ from oracle import edt_oracle
 pytestmark = pytest.mark.gpu
 
 # (batch, spatial): at least 512 groups of 16 lines in every strided pass
-CASES = [(1, (33, 40, 237)), (16, (17, 520)), (13, (511, 641)), (4, (31, 47, 95)), (40, (257, 207)), (1, (5, 160, 1650))]
+CASES = [(2, (33, 40, 237)), (16, (17, 520)), (13, (511, 641)), (4, (31, 47, 95)), (40, (257, 207)), (1, (5, 160, 1650))]
 
 
 @pytest.mark.parametrize("batch,spatial", CASES, ids=["%dx%s" % (b, "x".join(map(str, s))) for b, s in CASES])
@@ -35,5 +35,6 @@ def test_ragged_packed_lines(batch, spatial):
         names = {n for n, _ in binding.prof_read()}
     finally:
         binding.prof_enable(0)
-    assert any(n.startswith("line_search_pair") for n in names), names
+    assert "line_pair_rag_final" in names, names
+    assert nd == 2 or "line_pair_rag" in names, names
     check_against_oracle(mask, nd, None, res, edt_oracle.edt(mask, nd, None, nthreads=16))

@@ -119,7 +119,7 @@ def test_bracketed_search_keeps_no_order(p_bg):
     junk = np.arange(512, dtype=np.uint32)
     dist, names, ws, need = run_ws(mask, ws_fill=junk, ws_bytes=2048)
     assert need == 0
-    assert names == ["scan_word.o16", "line_search_final.i16"], names
+    assert names == ["scan_word.o16", "line_bracket_final.i16"], names
     assert np.array_equal(ws.view(np.uint32), junk)
     ora = edt_oracle.edt(mask, 2, None, want_sq=False, want_dist=True, nthreads=16)
     check_against_oracle(mask, 2, None, {"dist": dist}, ora)

@@ -87,7 +87,7 @@ def test_noalloc_whole_line_search_order():
         need = binding.tm_edt_workspace_size(2, spatial, batch)
         assert (need > 0) == ordered
         assert names == (["scan_word.cost.o16", "order", "line_search_final.i16"] if ordered
-                         else ["scan_word.o16", "line_search_final.i16"]), names
+                         else ["scan_word.o16", "line_bracket_final.i16"]), names
         ws = torch.zeros(max(1, need // 4), dtype=torch.int32, device=dev)
         ref = torch.empty_like(out)
         binding.tm_edt_ws(x, 2, None, ref, None, ws)
