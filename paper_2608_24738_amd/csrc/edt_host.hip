@@ -777,14 +777,10 @@ int run(Request &r) {
             s.idx = cidx;
             s.cstride = cstride;
             out = cidx;
-        } else if (r.unit) {
+        } else {   // unit sampling (sampled requests carry indices)
             mode = fh[nd - 2].bk ? kScanFieldL1 : kScanFieldInt;
             s.field_i = r.dist ? reinterpret_cast<int32_t *>(r.dist) : r.sq;
             out = s.field_i;
-        } else {
-            mode = kScanFieldFlt;
-            s.field_f = r.dist;
-            out = r.dist;
         }
         const bool word_ok = nlast % kWave == 0 && nlast <= uint32_t(kWave * kWave) &&
                              uintptr_t(r.in) % 16 == 0 && uintptr_t(out) % 16 == 0;
@@ -803,7 +799,6 @@ int run(Request &r) {
             ws.ndim = nd;
             ws.w = r.w[nd - 1];
             ws.field_i = s.field_i;
-            ws.field_f = s.field_f;
             ws.idx = s.idx;
             ws.cstride = s.cstride;
             ws.dist = s.dist;
@@ -847,7 +842,6 @@ int run(Request &r) {
                     else if (pkw) rc = TM_WORD_X("scan_word.o16", kScanFieldL1, 0, 8);
                     else rc = TM_WORD(kScanFieldL1);
                     break;
-                case kScanFieldFlt: rc = TM_WORD(kScanFieldFlt); break;
                 case kScanIndex: rc = TM_WORD(kScanIndex); break;
                 default: rc = TM_WORD(kScanFinal); break;
             }
@@ -867,7 +861,6 @@ int run(Request &r) {
             switch (mode) {
                 case kScanFieldInt: rc = launch("scan_span", k_scan_span<kScanFieldInt>, grid, block, 0, r.stream, s); break;
                 case kScanFieldL1: rc = launch("scan_span", k_scan_span<kScanFieldL1>, grid, block, 0, r.stream, s); break;
-                case kScanFieldFlt: rc = launch("scan_span", k_scan_span<kScanFieldFlt>, grid, block, 0, r.stream, s); break;
                 case kScanIndex: rc = launch("scan_span", k_scan_span<kScanIndex>, grid, block, 0, r.stream, s); break;
                 default: rc = launch("scan_span", k_scan_span<kScanFinal>, grid, block, 0, r.stream, s); break;
             }
@@ -878,7 +871,6 @@ int run(Request &r) {
             switch (mode) {
                 case kScanFieldInt: rc = launch("scan_long", k_scan_long<kScanFieldInt>, grid, block, lds, r.stream, s); break;
                 case kScanFieldL1: rc = launch("scan_long", k_scan_long<kScanFieldL1>, grid, block, lds, r.stream, s); break;
-                case kScanFieldFlt: rc = launch("scan_long", k_scan_long<kScanFieldFlt>, grid, block, lds, r.stream, s); break;
                 case kScanIndex: rc = launch("scan_long", k_scan_long<kScanIndex>, grid, block, lds, r.stream, s); break;
                 default: rc = launch("scan_long", k_scan_long<kScanFinal>, grid, block, lds, r.stream, s); break;
             }

@@ -13,7 +13,6 @@ namespace tmedt {
 
 enum ScanMode : int {
     kScanFieldInt = 0,   // int32 squared distance, kInfI if the line has no zero
-    kScanFieldFlt = 1,   // float w * squared distance, +inf if none
     kScanIndex = 2,      // int32 in-sample flat index of the zero, -1 if none
     kScanFinal = 3,      // rank-1 input: the line is the sample; final outputs
     kScanFieldL1 = 4     // int32 distance (taxicab / chessboard first pass), kInfI if none
@@ -31,7 +30,6 @@ struct ScanArgs {
     int32_t ndim;
     double w;              // squared sampling of the last axis
     int32_t *field_i;      // kScanFieldInt output (batch-flat)
-    float *field_f;        // kScanFieldFlt output (batch-flat)
     int32_t *idx;          // kScanIndex: the carrier, cstride elements per sample (slice 0 of
                            // [batch][ndim][vox], or a distance output holding flat indices);
                            // kScanFinal: coords
@@ -116,9 +114,6 @@ __device__ inline void scan_store(const ScanArgs &a, uint32_t gline, int x, int 
     if (MODE == kScanFieldInt || MODE == kScanFieldL1) {
         const int d = x - y;
         a.field_i[lbase + x] = y < 0 ? kInfI : MODE == kScanFieldL1 ? abs(d) : d * d;
-    } else if (MODE == kScanFieldFlt) {
-        const double d = double(x - y);
-        a.field_f[lbase + x] = y >= 0 ? float(a.w * (d * d)) : __builtin_inff();
     } else if (MODE == kScanIndex) {
         const uint32_t s = a.div_lps.div(gline);
         const uint64_t local = uint64_t(gline - s * a.lps) * a.n;
@@ -257,7 +252,7 @@ __global__ void __launch_bounds__(256) k_scan_span(ScanArgs a) {
                 }
             }
         }
-        if (MODE == kScanFieldFlt || MODE == kScanFinal || split) {
+        if (MODE == kScanFinal || split) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (p + j < valid)
@@ -275,7 +270,6 @@ template <int MODE>
 __device__ inline uint32_t *scan_slot(const ScanArgs &a, uint32_t gline, int x) {
     const uint64_t lbase = uint64_t(gline) * a.n;
     if (MODE == kScanFieldInt || MODE == kScanFieldL1) return reinterpret_cast<uint32_t *>(a.field_i + lbase + x);
-    if (MODE == kScanFieldFlt) return reinterpret_cast<uint32_t *>(a.field_f + lbase + x);
     if (MODE == kScanIndex) {
         const uint32_t s = a.div_lps.div(gline);
         const uint64_t local = uint64_t(gline - s * a.lps) * a.n;
@@ -389,7 +383,6 @@ struct WordScanArgs {
     int32_t ndim;
     double w;              // squared sampling of the last axis
     int32_t *field_i;      // kScanFieldInt output
-    float *field_f;        // kScanFieldFlt output
     int32_t *idx;          // kScanIndex: the carrier (see ScanArgs); kScanFinal: coords
     uint64_t cstride;      // kScanIndex: carrier elements per sample
     float *dist;           // kScanFinal outputs (each may be null)
@@ -493,10 +486,6 @@ __global__ void __launch_bounds__(256) k_scan_word(WordScanArgs a) {
             out[p] = none ? 0xffff : dd;
         } else if (MODE == kScanFieldInt || MODE == kScanFieldL1) {
             out[p] = none ? kInfI : (MODE == kScanFieldL1 ? dd : dd * dd);
-        } else if (MODE == kScanFieldFlt) {
-            const double df = double(dd);
-            out[p] = none ? __builtin_bit_cast(int32_t, __builtin_inff())
-                          : __builtin_bit_cast(int32_t, float(a.w * (df * df)));
         } else if (MODE == kScanIndex) {
             out[p] = none ? kNoIdx : int32_t(local + y);
         } else {
@@ -523,7 +512,7 @@ __global__ void __launch_bounds__(256) k_scan_word(WordScanArgs a) {
             db = a.idx;
             own = smp * a.cstride + local + uint64_t(w) * WB;
         } else {
-            db = MODE == kScanFieldFlt ? reinterpret_cast<int32_t *>(a.field_f) : a.field_i;
+            db = a.field_i;
             own = pos0;
         }
         if constexpr (PK) {
