@@ -231,6 +231,17 @@ constexpr uint32_t kBkMinRows = 640, kBkMinRowsPacked = 896;
 constexpr uint64_t kBkMinGroups = 400, kBkMinGroupsPacked = 512;
 constexpr uint32_t kBkMinWidth = 512;
 
+// Rows from which taxicab lines of any stride take the prefix and suffix minima
+// instead of the windowed search: below, a line leaves most lanes of its wave
+// without a row, and its distances are short.  Per call, us, windowed -> scan, for
+// half background, 1 % background, balls, one background pixel in 10000:
+//   300 x 30 x 91     13 -> 18, 14 -> 18, 14 -> 18, 16 -> 18
+//   300 x 48 x 91     14 -> 20, 16 -> 20, 15 -> 20, 21 -> 20
+//   300 x 70 x 90     18 -> 23, 20 -> 23, 20 -> 23, 29 -> 23
+//   150 x 100 x 102   21 -> 18, 22 -> 18, 23 -> 18, 31 -> 18
+//   30 x 400 x 401    33 -> 31, 36 -> 30, 59 -> 30, 76 -> 30
+constexpr uint32_t kL1MinRowsRag = 40;
+
 // Plan of one strided pass.
 struct FhPlan {
     uint32_t lpw;
@@ -478,10 +489,11 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
             const uint64_t cmax = r.metric == kL1 ? vmax + n + 4 : std::max<uint64_t>(vmax, n + 4);
             // taxicab whole lines: prefix and suffix minima, no search
             const void *cfield = r.sq;
-            if (r.metric == kL1 && n <= kL1MaxN && cmax < (uint64_t(1) << 29) && l1scan_lds(n) + 1024 <= kLdsBytes &&
-                total / n + kL1Lines < (uint64_t(1) << 32)) {
+            const bool l1rag = inner % kL1Lines != 0 || uintptr_t(cfield) % 16 != 0;
+            if (r.metric == kL1 && n <= kL1MaxN && n >= (l1rag ? kL1MinRowsRag : 1u) && cmax < (uint64_t(1) << 29) &&
+                l1scan_lds(n) + 1024 <= kLdsBytes && total / n + kL1Lines < (uint64_t(1) << 32)) {
                 p.l1scan = true;
-                p.l1rag = inner % kL1Lines != 0 || uintptr_t(cfield) % 16 != 0;
+                p.l1rag = l1rag;
                 p.lds = l1scan_lds(n);
                 continue;
             }

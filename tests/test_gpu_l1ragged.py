@@ -1,7 +1,8 @@
 """GPU parity of the taxicab whole-line pass on lines of any stride (groups of 8
 lines that are no multiple of the row, cross samples, or end past the last
 line), at the edges of the rows a lane holds (4, 8, 12, 16, 36 x 64), final and
-not.  Bit-exact against the oracle."""
+not; lines of fewer than 40 rows take the windowed search.  Bit-exact against the
+oracle."""
 import numpy as np
 import pytest
 
@@ -10,12 +11,15 @@ from oracle import edt_oracle
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(256, 7), (257, 33), (512, 9), (513, 129), (768, 1), (769, 5), (1024, 17), (1025, 3), (2304, 6),
-          (17, 31), (5, 300, 7)]
+SCAN, WINDOWED = "cdt_l1_scan", "cdt_line"
+# (spatial, kernel of each strided pass, the last axis but one first)
+SHAPES = [((256, 7), [SCAN]), ((257, 33), [SCAN]), ((512, 9), [SCAN]), ((513, 129), [SCAN]), ((768, 1), [SCAN]),
+          ((769, 5), [SCAN]), ((1024, 17), [SCAN]), ((1025, 3), [SCAN]), ((2304, 6), [SCAN]), ((40, 31), [SCAN]),
+          ((39, 31), [WINDOWED]), ((17, 31), [WINDOWED]), ((5, 300, 7), [SCAN, WINDOWED]), ((41, 300, 7), [SCAN, SCAN])]
 
 
-@pytest.mark.parametrize("spatial", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
-def test_ragged_taxicab(spatial):
+@pytest.mark.parametrize("spatial,passes", SHAPES, ids=["x".join(map(str, s)) for s, _ in SHAPES])
+def test_ragged_taxicab(spatial, passes):
     import torch
 
     from paper_2608_24738_amd import binding
@@ -33,5 +37,5 @@ def test_ragged_taxicab(spatial):
         names = [n for n, _ in binding.prof_read()]
     finally:
         binding.prof_enable(0)
-    assert "cdt_l1_scan_final" in names, names
+    assert names[1:] == passes[:-1] + [passes[-1] + "_final"], names
     assert np.array_equal(out.cpu().numpy(), edt_oracle.cdt(mask, len(spatial), "taxicab", nthreads=16))
