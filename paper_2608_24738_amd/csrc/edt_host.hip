@@ -215,18 +215,33 @@ constexpr uint64_t kLpMinGroupsRag = 512;
 // Distance passes take the bracketed search instead of the whole-line windowed
 // one, whose work grows with the distances, where lines and rows are long enough
 // for far distances and groups of 16 lines are many (a workgroup's phases are a
-// chain).  Measured (column pass, us, windowed -> bracketed; balls, discs, 1 %
-// background):
-//   8 x 1024^2          137 -> 67, 105 -> 54, 30 -> 30
-//   8 x 700 x 1024      65 -> 58, 103 -> 44, 21 -> 25 (packed rows: from 896)
-//   8 x 650 x 803       57 -> 54, 72 -> 48, 27 -> 24 (int32 rows: from 640)
-//   6 x 900 x 1024      103 -> 64, 88 -> 51, 21 -> 30 (384 groups)
-//   16 x 650 x 401      36 -> 50, 47 -> 46, 26 -> 29 (401 wide)
-//   4 x 720 x 500       22 -> 42, 30 -> 32, 13 -> 24 (125 groups)
+// chain).  Per call, us, windowed -> bracketed, for half background, 1 % background,
+// balls and discs (background):
+//                     euclidean                             chessboard
+//   8 x 1024^2        44-> 29  47-> 34  148-> 83  134-> 65  38-> 28  40-> 30  130-> 61  115-> 63
+//   9 x 900 x 800     38-> 33  41-> 39  104-> 81  117-> 65  33-> 31  35-> 35   91-> 62  102-> 61
+//   14 x 650 x 650    41-> 40  43-> 43   92-> 73   76-> 71  37-> 38  38-> 40   80-> 69   67-> 67
+//   16 x 900 x 530    49-> 45  51-> 50   75-> 88   97-> 85  44-> 43  45-> 45   65-> 76   88-> 79
+//   16 x 1024 x 512   43-> 28  47-> 33   67-> 75  100-> 62  37-> 26  40-> 29   58-> 59   89-> 59
+//   4 x 2000 x 1800   97-> 99 103->110  424->196  390->164  89-> 97  93->100  366->157  325->152
+//   2 x 900 x 4001    73-> 65  76-> 69   94->109  343->104  69-> 65  71-> 66   84-> 87  280-> 95
+// (past 1780 rows one workgroup fills a compute unit; short distances over few
+// such lines are what the brackets do not gain on).  Left to the windowed search:
+//   13 x 640 x 640    36-> 35  38-> 41   85-> 68   73-> 66  31-> 33  32-> 37   75-> 65   63-> 63
+//   8 x 700 x 1024    30-> 23  32-> 26   72-> 66  114-> 52  25-> 22  27-> 24   63-> 49   99-> 50
+//   5 x 660 x 1024    22-> 18  24-> 21   49-> 57   70-> 47  18-> 17  20-> 19   42-> 42   62-> 43
+//   6 x 900 x 1024    28-> 24  31-> 30  106-> 69   95-> 56  24-> 23  26-> 26   96-> 53   85-> 51
+//   1 x 1024 x 4096   26-> 24  28-> 28   50-> 69  131-> 50  23-> 23  24-> 25   42-> 44  115-> 46
+//   6 x 650 x 803     28-> 28  30-> 31   60-> 59   55-> 55  25-> 27  26-> 29   52-> 50   48-> 49
+//   16 x 650 x 401    35-> 31  37-> 34   46-> 60   59-> 56  32-> 30  33-> 32   41-> 52   51-> 53
+//   4 x 720 x 500     17-> 19  18-> 21   26-> 44   34-> 36  15-> 18  16-> 19   23-> 34   29-> 34
 // Rows of a multiple of 64 are packed to 16 bits for the windowed search, which
-// moves their lines up.  Index passes take the brackets where the tiled search
-// ends (256 rows): the envelope with one lane per line takes 516 us on
-// 16 x 375 x 500 balls, the brackets 40 us.
+// moves their lines up (896 rows, 512 groups).  Those are drawn so that no mask
+// loses much, and so leave gains behind: 700 to 900 packed rows of 1024, and 256 to
+// 512 groups of them, gain on every mask, while the same counts of rows and
+// groups in other proportions lose (5 x 660 x 1024, 1 x 1024 x 4096).  Index passes
+// take the brackets where the tiled search ends (256 rows): the envelope with one
+// lane per line takes 516 us on 16 x 375 x 500 balls, the brackets 40 us.
 constexpr uint32_t kBkMinRows = 640, kBkMinRowsPacked = 896;
 constexpr uint64_t kBkMinGroups = 400, kBkMinGroupsPacked = 512;
 constexpr uint32_t kBkMinWidth = 512;
@@ -552,9 +567,10 @@ int plan_passes(const Request &r, uint64_t total, bool index_path, FhPlan *fh) {
         }
         // Unit sampling without indices, lines of up to 512 rows: 16 lines per
         // workgroup, two per packed 16-bit word, while that fills the chip and
-        // every exact candidate stays in int32.  Vector loads and stores where lines of a multiple of 16 rows
-        // have their 16 neighbours adjacent in memory (lp16), else one element
-        // per lane (lprag).
+        // every exact candidate stays in int32.  Vector loads and stores where
+        // lines of a multiple of 16 rows have their 16 neighbours adjacent in
+        // memory and the buffer is aligned (lp16), else one element per lane
+        // (lprag).
         if (!index_path && r.unit && n <= kLpMaxN) {
             uint64_t inner = 1;
             for (int b = a + 1; b < nd; ++b) inner *= r.shape[b];

@@ -46,9 +46,9 @@ struct LinePairArgs {
     int32_t *buf;          // int32 field, batch-flat, in place (kInfI = no site)
     float *dist;           // final pass: outputs (each may be null)
     int32_t *sq;
-    uint32_t lines;        // lines of this pass (a multiple of 16)
-    uint32_t n;            // line length, a multiple of 16, at most kLpMaxN
-    uint32_t inner;        // element stride of the line, a multiple of 16
+    uint32_t lines;        // lines of this pass (a multiple of 16 unless RAG)
+    uint32_t n;            // line length, at most kLpMaxN (a multiple of 16 unless RAG)
+    uint32_t inner;        // element stride of the line (a multiple of 16 unless RAG)
     Div32 div_inner;
     uint32_t mult;         // order of the sets of 4 line groups (coprime to their count)
     const uint32_t *order; // null, or the line group of each workgroup (a permutation, k_order)
@@ -213,7 +213,8 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
         line_i[t] = i0;
     }
 
-    // ---- stage: thread t holds lines 8 (t & 1) .. + 7 of rows t / 2, t / 2 + 512, ...
+    // ---- stage: thread t holds lines 8 (t & 1) .. + 7 of rows t / 2, t / 2 + nthreads / 2, ...
+    // (RAG: line t % 16 of rows t / 16, t / 16 + nthreads / 16, ...)
     if (t == 0) {
         claim = 0;
         site_rows = 0;

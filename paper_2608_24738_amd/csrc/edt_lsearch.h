@@ -11,18 +11,18 @@
 // d), so a search outward from q can stop once the best value found is no
 // larger than that.  The result is the same minimum the lower envelope gives.
 //
-// A workgroup of 16 waves owns LPW adjacent lines (8, or 4 for the longest
-// lines) and stages them whole in LDS, [row][line], as 16-bit values when
-// every value plus any in-line distance term stays below the 16-bit "no
-// site" code, else 32-bit.  Lane l of a wave takes line l % LPW at row
-// (wave row) + l / LPW: a wave covers a compact patch of consecutive rows,
-// whose search lengths differ little (the result is 1-Lipschitz along the
-// line), and reads 64 consecutive entries (conflict-free) at every step.
-// Search steps come in eights between wave-wide stop votes, read from two
-// bases clamped into the guard rows (which hold "no site").  Results go
-// straight to global memory: the staged copy is what every search reads, and
-// no other workgroup reads these lines.  Fewer lines per workgroup give more
-// workgroups when there are few lines.
+// A workgroup of up to 16 waves (no more than its lines have steps of rows to
+// search) owns LPW adjacent lines (8, or 4 for the longest lines) and stages
+// them whole in LDS, [row][line], as 16-bit values when every value plus any
+// in-line distance term stays below the 16-bit "no site" code, else 32-bit.
+// Lane l of a wave takes line l % LPW at row (wave row) + l / LPW: a wave
+// covers a compact patch of consecutive rows, whose search lengths differ
+// little (the result is 1-Lipschitz along the line), and reads 64 consecutive
+// entries (conflict-free) at every step.  Search steps come in eights between
+// wave-wide stop votes, read from two bases clamped into the guard rows (which
+// hold "no site").  Results go straight to global memory: the staged copy is
+// what every search reads, and no other workgroup reads these lines.  Fewer
+// lines per workgroup give more workgroups when there are few lines.
 //
 // A workgroup whose lines all hold at most kLsDirect sites (rows holding a
 // value) skips the search: each element takes the minimum over its line's
@@ -251,8 +251,8 @@ __global__ void __launch_bounds__(kWave * kLsWaves) k_line_search(LineSearchArgs
     }
     __syncthreads();
     // A workgroup whose lines all have at most kLsDirect sites (uniform test)
-    // takes the direct minimum: wave w lists the site rows of line w, 64 rows
-    // per ballot.
+    // takes the direct minimum: the waves list the site rows of the lines in
+    // turn, 64 rows per ballot.
     bool few = DIRECT;
 #pragma unroll
     for (int k = 0; k < LPW; ++k) few &= has_site[k] <= uint32_t(kLsDirect);
