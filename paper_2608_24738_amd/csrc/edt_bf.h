@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(kBfThreads) k_dt_bf(BfArgs a) {
             const uint32_t d4[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int j = 0; j < PB / 4; ++j) y.w[j] = d4[j];
-        } else if (p + PB <= a.vox && (uintptr_t(m) + p) % 4 == 0) {
+        } else if (PB == kBfBytesMany && p + PB <= a.vox && (uintptr_t(m) + p) % 4 == 0) {
 #pragma unroll
             for (int j = 0; j < PB / 4; ++j) y.w[j] = reinterpret_cast<const uint32_t *>(m + p)[j];
         } else {
