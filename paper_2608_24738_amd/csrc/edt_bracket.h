@@ -34,9 +34,11 @@
 //      that jump from one object's rows to another's) a block of 8 rows is
 //      walked only when its smallest d could improve some row of the lane.
 //
-// Bound by VALU issue and the spread of work over the workgroups (two per
-// compute unit for 8 x 1024^2): column pass of 8 x 1024^2 discs 105 -> 54 us,
-// chessboard 90 -> 49 us; index pass of 16 x 375 x 500 516 -> 41 us.  Segments of
+// Bound by VALU issue (147 instructions per element, 60 % of the issue time) and
+// the spread of work over the workgroups (two per compute unit for 8 x 1024^2,
+// all at once): column pass of 8 x 1024^2 discs, windowed and ordered against
+// bracketed, 83 -> 52 us, chessboard 71 -> 46 us, one background pixel 31 -> 15 us;
+// index pass of 16 x 375 x 500 516 -> 39 us (43 % of the issue time).  Segments of
 // 12 or 16 rows (larger walks, spills) and a top anchor per 4 or 16 segments
 // measured the same or slower.
 // Walking a row outside a lane's bracket is harmless (it is a candidate like
