@@ -176,6 +176,7 @@ __global__ void __launch_bounds__(1024, 8) k_line_bracket(BracketArgs a) {
                 seen[k] |= as_word(s);
                 any = any || as_word(s) != 0u;
             }
+            // (both halves of a row hold a site or none does: it lies in one image row)
             const bool row_any = any || __shfl_xor(int(any), 1) != 0;
             if (row_any && h == 0) {
                 const uint32_t k = atomicAdd(&site_rows, 1u);

@@ -280,7 +280,9 @@ __global__ void __launch_bounds__(kPsThreads, 8) k_line_pair16(LinePairArgs a) {
             code[(r + kLpG) * kLpRS + 4 * h + k] = c16(v[2 * k]) | (c16(v[2 * k + 1]) << 16);
             any = any || v[2 * k] != kInfI || v[2 * k + 1] != kInfI;
         }
-        // a row holds a site when either of its two threads sees one
+        // a row holds a site when either of its two threads sees one (in fact both
+        // or none do: every later axis has been processed, so "no site" is the
+        // same for all lines of a row)
         const bool row_any = any || __shfl_xor(int(any), 1) != 0;
         if (row_any && h == 0) {
             const uint32_t k = atomicAdd(&site_rows, 1u);
